@@ -12,8 +12,8 @@
 //   perm   gather positions, velocities, ids into scratch in the new order
 //   back   copy back; inverse permutation
 //   list   per force tile (tiles.h): its segment and halo run table, then
-//          per atom the 3^dim neighbouring cells, keeping every image pair
-//          within rc_ab + skin; tiles with an LDS halo get the packed list
+//          per cell of it the atoms against the 3^dim neighbouring cells,
+//          keeping every image pair within rc_ab + skin; tiles with an LDS halo get the packed list
 //          (16-bit byte offsets 8 h of the neighbour's halo slot h), the
 //          others the word list (j | image code << 24); engine.h
 //   done   reset the validity bound of each rebuilt slot
@@ -228,14 +228,66 @@ __global__ __launch_bounds__(kBlock) void k_rb_back(RebuildArgs a) {
   if (a.alt4) a.alt4[gi] = a.talt4[gi];
 }
 
-// Neighbour lists, one block per force tile (tiles.h): the tile's segment
-// and candidate runs are computed here; the scan marks every candidate some
-// list names, the marked candidates numbered in order form the compact halo
-// (stored for the force kernel as j | code << 24), and each entry is the
-// byte offset of its compact halo slot (or, for a tile whose compact halo
-// does not fit in LDS, the neighbour's global index and image code).
+// Neighbour lists, one block per force tile (tiles.h).  The tile's segment and
+// candidate runs are computed here.  A cell's atoms share their candidates:
+// per neighbouring row one contiguous range of candidate numbers (the wrapped
+// cells' runs are numbered next to their row's), 3 or 9 ranges that a cell
+// numbers on its own, in chunks of 64.
+//   test     a wavefront takes up to kUnitAtoms atoms of one cell and walks
+//            the cell's chunks, one candidate per lane (loaded a chunk ahead
+//            and turned into an FP32 offset from the tile's first atom), the
+//            atoms one after another: the ballot of the distance test is the
+//            atom's neighbour mask of the chunk, kept in LDS.  Every
+//            candidate that some mask names is flagged.
+//   number   the flagged candidates in order form the compact halo (stored for
+//            the force kernel as j | code << 24) and their bit counts give each
+//            its halo slot.
+//   write    a lane takes half of the A or of the B neighbours of one atom in the tile's
+//            walk order, turns its masks' bits into byte offsets of halo slots
+//            through the cell's table and stores whole groups; the lanes of a
+//            wavefront store neighbouring columns.
+// The test is bound by its vector instructions: about 12 per atom and chunk,
+// 64 pairs.  One candidate per lane keeps every lane busy, where a lane per atom
+// left over half of the block idle, read each candidate from LDS once for
+// every atom and sent each entry to memory twice, one by one.  Rebuild of 16 x
+// 32768 atoms (3D, up to 16 of them at once): 535 us, 2246 before; of one
+// replica 67, 256 before.
+// A tile whose compact halo does not fit in the force kernel's LDS gets word
+// lists (j | code); so does a tile past the limits below, tested in FP64
+// straight from the cells (kernel's end).
+constexpr int kListBlock = 512;     // threads of the list kernel
+constexpr int kChunkParts = 2;      // a unit's chunks are split over this many wavefronts
+constexpr int kUnitAtoms = 16;      // atoms of one cell that a wavefront tests together
+constexpr int kListCells = 96;      // cells a tile may span
+constexpr int kCellChunks = 32;     // chunks of one cell's candidates
+constexpr int kTileChunks = 128;    // ... of all the tile's cells
+constexpr int kMaskWords = 2048;    // masks kept at once; larger tiles go in batches of atoms
+
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_scan(int v) {
+  const int lane = threadIdx.x % kWave;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int u = __shfl_up(v, o, kWave);
+    if (lane >= o) v += u;
+  }
+  return v;
+}
+
+// Counts v[0 .. n - 1] to their exclusive sums v[0 .. n], n <= kListCells, by
+// one wavefront.
+__device__ __forceinline__ void scan_cells(uint16_t* v, int n) {
+  static_assert(kListCells <= 2 * kWave, "two cells per lane");
+  const int lane = threadIdx.x % kWave;
+  const int c0 = 2 * lane < n ? v[2 * lane] : 0, c1 = 2 * lane + 1 < n ? v[2 * lane + 1] : 0;
+  const int before = wave_scan(c0 + c1) - (c0 + c1);
+  if (2 * lane <= n) v[2 * lane] = (uint16_t)before;
+  if (2 * lane + 1 <= n) v[2 * lane + 1] = (uint16_t)(before + c0);
+  if (lane == kWave - 1 && n == 2 * kWave) v[n] = (uint16_t)(before + c0 + c1);
+}
+
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_rb_list(RebuildArgs a) {
+__global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_rb_list(RebuildArgs a) {
   const int2 bt = a.tiles[blockIdx.x];
   if (bt.x < 0) return;
   const State* st = a.state + bt.x;
@@ -245,83 +297,391 @@ __global__ __launch_bounds__(kBlock) void k_rb_list(RebuildArgs a) {
   const int nc[3] = {st->nc[0], st->nc[1], st->nc[2]};
   const int32_t* cs = a.cell_start + g.cell_off;
   const double4* P = a.pos4 + g.atom_off;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  constexpr int CAP = (D == 3) ? kHaloCap3 : kHaloCap2;
+  constexpr int R = (D == 3) ? 9 : 3;        // neighbouring rows of a cell
+  constexpr int R0 = (D == 3) ? 0 : 3;       // first of them among the runs' rows
+  constexpr int NW = kListBlock / kWave;
   __shared__ TileRun runs[kRuns];
-  __shared__ int s_cx0, s_cx1, s_cand, s_lds, s_ncand;
-  __shared__ uint32_t s_bits[kHaloWords];   // candidates named by some list
-  __shared__ int s_pre[kHaloWords];          // marked candidates before each word
+  __shared__ double s_sh[kRuns][3];          // image shifts
+  __shared__ int s_c0[kRuns / 3];            // first cell of each neighbouring row
+  __shared__ int s_cx0, s_cx1, s_ncand, s_words, s_halo;
+  __shared__ int s_cs[kListCells + 1];       // first atom of each cell of the tile
+  __shared__ uint16_t s_lo[kListCells][R];   // a cell's ranges: first candidate
+  __shared__ uint16_t s_p[kListCells][R + 1];  // ... and its number within the cell
+  __shared__ uint16_t s_cb[kListCells + 1];  // first chunk of each cell
+  __shared__ uint16_t s_uo[kListCells + 1];  // first unit of each cell
+  __shared__ unsigned long long s_mask[kMaskWords];
+  __shared__ unsigned long long s_ta[kTileChunks];   // candidates of type A
+  __shared__ uint16_t s_map[kTileChunks * kWave];    // candidate, then byte offset of its halo slot
+  __shared__ __align__(8) uint8_t s_flag[kCandCap];  // candidates named by some list
+  __shared__ unsigned long long s_bits[kCandCap / kWave];
+  __shared__ int s_pre[kCandCap / kWave];
+  __shared__ float4 s_atom[NW][kUnitAtoms];  // the atoms of each wavefront's unit
+  __shared__ int s_cnt0[kTileSort];          // list counts in tile order
+  __shared__ uint16_t s_rank[kTileSort];     // walk order: rank of an atom, then (s_src) atom of a rank
+  __shared__ uint16_t s_src[kTileSort];
+  __shared__ uint8_t s_cell[kTileSort];      // cell of an atom
   int a0, a1, cy, cz;
   segment(nc, st->tiles_x, cs, bt.y, a0, a1, cy, cz);
+  const int nt = a1 - a0;
+  const int64_t tix = g.tile_off + bt.y;
+  const int row0 = (cz * nc[1] + cy) * nc[0];
   if (tid == 0) {
-    int c3[3];
     s_cx0 = 0;
     s_cx1 = 0;
-    if (a1 > a0) {
-      cell_of_pos<D>(bx, nc, P[a0], c3);
-      s_cx0 = c3[0];
-      cell_of_pos<D>(bx, nc, P[a1 - 1], c3);
-      s_cx1 = c3[0];
+  }
+  __syncthreads();
+  if (nt > 0)
+    for (int x = tid; x < nc[0]; x += kListBlock) {
+      const int b = cs[row0 + x], e = cs[row0 + x + 1];
+      if (b <= a0 && a0 < e) s_cx0 = x;
+      if (b < a1 && a1 <= e) s_cx1 = x;
+    }
+  __syncthreads();
+  const int cx0 = s_cx0, ncell = s_cx1 - s_cx0 + 1;
+  if (tid < kRuns) {
+    runs[tid] = make_run<D>(tid, cx0, s_cx1, cy, cz, nc, cs);
+    code_shift(tid, bx, s_sh[tid]);
+  }
+  if (tid < kRuns / 3) {
+    const int ry = cy + tid % 3 - 1, rz = (D == 3) ? cz + tid / 3 - 1 : 0;
+    const int y = ry < 0 ? ry + nc[1] : (ry >= nc[1] ? ry - nc[1] : ry);
+    const int z = rz < 0 ? rz + nc[2] : (rz >= nc[2] ? rz - nc[2] : rz);
+    s_c0[tid] = (z * nc[1] + y) * nc[0];
+  }
+  for (int i = tid; i < min(nt, kTileSort); i += kListBlock) s_cnt0[i] = 0;
+  for (int h = tid; h < kCandCap / 8; h += kListBlock) reinterpret_cast<uint64_t*>(s_flag)[h] = 0u;
+  __syncthreads();
+  if (wv == 0) {
+    const int c = lane < kRuns ? runs[lane].count : 0;
+    const int inc = wave_scan(c);
+    if (lane < kRuns) runs[lane].off = inc - c;
+    if (lane == kWave - 1) {
+      s_ncand = inc;
+      s_words = 0;
     }
   }
   __syncthreads();
-  if (tid < kRuns) runs[tid] = make_run<D>(tid, s_cx0, s_cx1, cy, cz, nc, cs);
-  for (int w = tid; w < kHaloWords; w += kBlock) s_bits[w] = 0u;
-  __syncthreads();
-  constexpr int CAP = (D == 3) ? kHaloCap3 : kHaloCap2;
-  const int64_t tix = g.tile_off + bt.y;
-  const int nt = a1 - a0;
-  const bool sortable = nt <= kTileSort;
-  if (tid == 0) {
-    int off = 0;
-    for (int r = 0; r < kRuns; ++r) {
-      runs[r].off = off;
-      off += runs[r].count;
-    }
-    s_ncand = off;
-    s_cand = (st->list_mode == 0 && off <= 32 * kHaloWords && sortable) ? 1 : 0;
-  }
-  __syncthreads();
-  // cand: entries hold candidate numbers during the scan and become compact
-  // halo offsets (or global entries) below
-  const bool cand = s_cand != 0;
   const int ncand = s_ncand;
-  // Work area: the staged candidates during the scan, the staged list rows
-  // in the final pass.  Candidates are FP32 offsets from the tile's first
-  // atom with their image shift applied, and their types.
-  __shared__ __align__(16) unsigned char s_work[kCandCap * (4 * D + 1)];
-  float* s_cx = reinterpret_cast<float*>(s_work);
-  float* s_cy = s_cx + kCandCap;
-  float* s_cz = s_cy + kCandCap;                      // 3D only
-  uint8_t* s_ct = reinterpret_cast<uint8_t*>(s_cx + D * kCandCap);
-  __shared__ int s_cnt0[kTileSort];   // list counts in tile order
-  const double4 ref = nt > 0 ? P[a0] : make_double4(0.0, 0.0, 0.0, 0.0);
-  if (cand) {
-    for (int hc = tid; hc < ncand; hc += kBlock) {
-      int r = 0;
-      while (r < kRuns - 1 && !(hc >= runs[r].off && hc < runs[r].off + runs[r].count)) ++r;
-      const double4 pj = P[runs[r].src + (hc - runs[r].off)];
-      double sft[3];
-      code_shift(runs[r].code, bx, sft);
-      s_cx[hc] = (float)((pj.x + sft[0]) - ref.x);
-      s_cy[hc] = (float)((pj.y + sft[1]) - ref.y);
-      if (D == 3) s_cz[hc] = (float)((pj.z + sft[2]) - ref.z);
-      s_ct[hc] = (uint8_t)pj.w;
+  bool fast = st->list_mode == 0 && ncand <= kCandCap && nt <= kTileSort && ncell <= kListCells;
+  // the cells' ranges
+  if (fast) {
+    for (int ci = tid; ci <= ncell; ci += kListBlock) s_cs[ci] = cs[row0 + cx0 + ci];
+    for (int e = tid; e < ncell * R; e += kListBlock) {
+      const int ci = e / R, q = e % R, cx = cx0 + ci, r = 3 * (q + R0), c0 = s_c0[q + R0];
+      const TileRun m = runs[r + 1];
+      s_lo[ci][q] = (uint16_t)(cx > 0 ? m.off + (cs[c0 + cx - 1] - m.src) : runs[r].off);
+      const int hi = cx + 1 < nc[0] ? m.off + (cs[c0 + cx + 2] - m.src) : runs[r + 2].off + runs[r + 2].count;
+      s_p[ci][q + 1] = (uint16_t)(hi - s_lo[ci][q]);
     }
     __syncthreads();
+    for (int ci = tid; ci < ncell; ci += kListBlock) {
+      int acc = 0;
+      s_p[ci][0] = 0;
+      for (int q = 1; q <= R; ++q) {
+        acc += s_p[ci][q];
+        s_p[ci][q] = (uint16_t)acc;
+      }
+      const bool any = min(s_cs[ci + 1], a1) > max(s_cs[ci], a0);   // atoms of the tile in the cell
+      const int ch = any ? (acc + kWave - 1) / kWave : 0;
+      s_cb[ci] = (uint16_t)ch;
+      atomicMax(&s_words, ch);
+    }
+    __syncthreads();
+    if (wv == 0) scan_cells(s_cb, ncell);
+    __syncthreads();
+    fast = s_words <= kCellChunks && s_cb[ncell] <= kTileChunks;
   }
-  for (int li = a0 + tid; li < a1; li += kBlock) {
+  const int words = max(s_words, 1);
+  const double4 ref = nt > 0 ? P[a0] : make_double4(0.0, 0.0, 0.0, 0.0);
+  const int batch = max(1, min(nt, kMaskWords / words));   // atoms whose masks fit at once
+  const int G = a.max_nb / kGroup;
+  if (fast) {
+    // list distance (squared, with the margin) of an atom's type t and a candidate's type
+    float thr[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const double rc = sqrt(a.pp[2 * t + u].rc2) + a.skin;
+        thr[t][u] = (float)((rc + kListMargin) * (rc + kListMargin));
+      }
+    // j | image code of a candidate
+    auto global_entry = [&](int hc) {
+      int r = R0;   // its row: the last that starts no later
+#pragma unroll
+      for (int k = 1; k < R; ++k) r += runs[3 * (R0 + k)].off <= hc ? 1 : 0;
+      const TileRun m = runs[3 * r + 1];
+      const TileRun rr = runs[3 * r + (hc >= m.off ? 1 : 0) + (hc >= m.off + m.count ? 1 : 0)];
+      return (uint32_t)(rr.src + (hc - rr.off)) | ((uint32_t)rr.code << kCodeShift);
+    };
+    auto slot_of = [&](int hc) {
+      const int w = hc / kWave;
+      return s_pre[w] + __popcll(s_bits[w] & ((1ull << (hc % kWave)) - 1ull));
+    };
+    constexpr uint32_t fill = 8u * (uint32_t)(CAP - 1);
+    bool lds = true;
+    // Steps 0 .. nbatch - 1 test the atoms, a batch each (counts, candidate tables
+    // and flags with them), the last of them numbers the candidates, and
+    // the steps after it write the lists (of several batches, tested again first).
+    const int nbatch = max(1, (nt + batch - 1) / batch);
+    for (int step = 0; step < 2 * nbatch; ++step) {
+      const bool first = step < nbatch;
+      const int b0 = (step % nbatch) * batch, b1 = min(nt, b0 + batch);
+      __syncthreads();
+      if (first || nbatch > 1) {
+        for (int ci = tid; ci < ncell; ci += kListBlock)
+          s_uo[ci] = (uint16_t)(max(0, min(s_cs[ci + 1], a0 + b1) - max(s_cs[ci], a0 + b0) + kUnitAtoms - 1) /
+                                kUnitAtoms);
+        __syncthreads();
+        if (wv == 0) scan_cells(s_uo, ncell);
+        __syncthreads();
+        const int nunit = s_uo[ncell];
+        for (int item = wv; item < kChunkParts * nunit; item += NW) {
+          const int u = item / kChunkParts;
+          // the unit's cell: the last whose first unit is not past u
+          int ci = -1;
+          for (int c0 = 0; c0 < ncell; c0 += kWave)
+            ci += __popcll(__ballot(c0 + lane < ncell && (int)s_uo[c0 + lane] <= u));
+          ci = __builtin_amdgcn_readfirstlane(ci);
+          // the cell's atoms in nearly equal units
+          const int y0 = max(s_cs[ci], a0 + b0), y1 = min(s_cs[ci + 1], a0 + b1);
+          const int uc = u - (int)s_uo[ci], nu = (int)s_uo[ci + 1] - (int)s_uo[ci];
+          const int x0 = y0 + uc * (y1 - y0) / nu;
+          const int cnt = __builtin_amdgcn_readfirstlane(y0 + (uc + 1) * (y1 - y0) / nu - x0);
+          const int total = __builtin_amdgcn_readfirstlane(s_p[ci][R]), cb = s_cb[ci];
+          const int nch = (total + kWave - 1) / kWave;
+          // this item's share of the chunks
+          const int ch0 = item % kChunkParts * nch / kChunkParts,
+                    ch1 = (item % kChunkParts + 1) * nch / kChunkParts;
+          if (ch0 == ch1) continue;
+          // the cell's tables are written by the first unit that sees the cell
+          const bool tables = first && x0 == max(s_cs[ci], a0);
+          // lane q < cnt: atom x0 + q, its own number among the cell's candidates
+          int aw = 0;
+          int na = 0, nb = 0;
+          float4 at = make_float4(1e18f, 0.f, 0.f, 0.f);   // past the unit: no candidate is near
+          if (lane < cnt) {
+            const double4 pi = P[x0 + lane];
+            at.x = (float)(pi.x - ref.x);
+            at.y = (float)(pi.y - ref.y);
+            at.z = (D == 3) ? (float)(pi.z - ref.z) : 0.0f;
+            at.w = (float)pi.w;
+            constexpr int q0 = R / 2;            // the atom's own row
+            const TileRun m = runs[3 * (q0 + R0) + 1];
+            const int own = m.off + (x0 + lane - m.src) - (int)s_lo[ci][q0] + (int)s_p[ci][q0];
+            aw = own;
+            if (first) s_cell[x0 + lane - a0] = (uint8_t)ci;
+          }
+          if (lane < kUnitAtoms) s_atom[wv][lane] = at;
+          int sp[R];
+#pragma unroll
+          for (int q = 1; q < R; ++q) sp[q] = s_p[ci][q];
+          // this lane's candidate of chunk ch, loaded
+          auto load = [&](int ch, int& hc, int& code, double4& pj) {
+            const int p = ch * kWave + lane;
+            int q = 0;   // the range that holds number p
+#pragma unroll
+            for (int k = 1; k < R; ++k) q += p >= sp[k] ? 1 : 0;
+            hc = p < total ? p + (int)s_lo[ci][q] - (int)s_p[ci][q] : -1;
+            if (hc >= 0) {
+              const int r = 3 * (q + R0);
+              const TileRun m = runs[r + 1];
+              const TileRun rr = runs[r + (hc >= m.off ? 1 : 0) + (hc >= m.off + m.count ? 1 : 0)];
+              code = rr.code;
+              pj = P[rr.src + (hc - rr.off)];
+            }
+          };
+          int hc_n = -1, code_n = 13;
+          double4 pj_n = make_double4(0.0, 0.0, 0.0, 0.0);
+          load(ch0, hc_n, code_n, pj_n);
+          for (int ch = ch0; ch < ch1; ++ch) {
+            const int hc = hc_n, code = code_n;
+            const double4 pj = pj_n;
+            if (ch + 1 < ch1) load(ch + 1, hc_n, code_n, pj_n);
+            const float px = (float)((pj.x + s_sh[code][0]) - ref.x);
+            const float py = (float)((pj.y + s_sh[code][1]) - ref.y);
+            const float pz = (D == 3) ? (float)((pj.z + s_sh[code][2]) - ref.z) : 0.0f;
+            const bool tb = pj.w != 0.0;
+            // a lane without a candidate passes no test
+            const float t0 = hc < 0 ? -1.0f : (tb ? thr[0][1] : thr[0][0]);
+            const float t1 = hc < 0 ? -1.0f : (tb ? thr[1][1] : thr[1][0]);
+            unsigned long long any = 0ull;
+            unsigned long long mine = 0ull;   // lane q: the mask of atom q
+            for (int q0 = 0; q0 < cnt; q0 += 4) {
+              float4 x[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) x[q] = s_atom[wv][q0 + q];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const float fx = px - x[q].x, fy = py - x[q].y, fz = (D == 3) ? pz - x[q].z : 0.0f;
+                const float t = x[q].w != 0.0f ? t1 : t0;
+                const unsigned long long m = __ballot(fx * fx + fy * fy + fz * fz < t);
+                any |= m;
+                mine = lane == q0 + q ? m : mine;
+              }
+            }
+            const unsigned long long ta = __ballot(hc >= 0 && !tb);
+            if (lane < cnt) {
+              if (aw / kWave == ch) mine &= ~(1ull << (aw % kWave));   // not its own neighbour
+              s_mask[(x0 - a0 - b0 + lane) * words + ch] = mine;
+              na += __popcll(mine & ta);
+              nb += __popcll(mine & ~ta);
+            }
+            if (first) {
+              if ((any >> lane) & 1ull) s_flag[hc] = 1;
+              if (tables) {
+                s_map[(cb + ch) * kWave + lane] = (uint16_t)max(hc, 0);
+                if (lane == 0) s_ta[cb + ch] = ta;
+              }
+            }
+          }
+          if (first && lane < cnt) atomicAdd(&s_cnt0[x0 - a0 + lane], na | (nb << 16));
+        }
+        __syncthreads();
+      }
+      if (first) {
+        if (step < nbatch - 1) continue;
+        for (int i = tid; i < nt; i += kListBlock) {
+          // both segments' groups have to fit side by side in the packed list
+          const int na = s_cnt0[i] & 0xffff, nb = s_cnt0[i] >> 16;
+          if (na + nb > a.max_nb || (na + kGroup - 1) / kGroup + (nb + kGroup - 1) / kGroup > G) {
+            atomicMax(a.overflow, na + nb);
+            s_cnt0[i] = 0;
+          }
+        }
+        // number the flagged candidates
+        const int nw = (ncand + kWave - 1) / kWave;
+        for (int w = wv; w < nw; w += NW) {
+          const int h = w * kWave + lane;
+          const unsigned long long m = __ballot(h < ncand && s_flag[h] != 0);
+          if (lane == 0) s_bits[w] = m;
+        }
+        __syncthreads();
+        if (wv == 0) {
+          const int c = lane < nw ? __popcll(s_bits[lane]) : 0;
+          const int inc = wave_scan(c);
+          if (lane < nw) s_pre[lane] = inc - c;
+          if (lane == kWave - 1) s_halo = inc;
+        }
+        __syncthreads();
+        // LDS halo slot CAP - 1 is the force kernel's far fill slot
+        const int halo = s_halo;
+        lds = halo < CAP;
+        if (tid == 0) {
+          TileHdr h;
+          h.a0 = a0;
+          h.a1 = a1;
+          h.pad_ = 0;
+          h.halo = lds ? halo : -1;
+          a.thdr[tix] = h;
+        }
+        if (lds) {
+          uint32_t* hx = a.hidx + tix * CAP;
+          for (int hc = tid; hc < ncand; hc += kListBlock)
+            if (s_flag[hc]) hx[slot_of(hc)] = global_entry(hc);
+          for (int e = tid; e < s_cb[ncell] * kWave; e += kListBlock)
+            s_map[e] = (uint16_t)(8 * slot_of(s_map[e]));
+        }
+        // Walk order.  The consumers of a tile with an LDS halo walk its atoms by
+        // decreasing list length (ties by position), so the lanes of a wavefront
+        // have lists of similar length: tord[a0 + k] is the k-th atom, and its
+        // packed list and count sit in column a0 + k, so a wavefront still reads
+        // consecutive list words.  Other tiles keep their atoms in tile order.
+        for (int i = tid; i < nt; i += kListBlock) {
+          const int ci = (s_cnt0[i] & 0xffff) + (s_cnt0[i] >> 16);
+          int rank = i;
+          if (lds) {
+            rank = 0;
+            for (int k = 0; k < nt; ++k) {
+              const int cj = (s_cnt0[k] & 0xffff) + (s_cnt0[k] >> 16);
+              rank += (cj > ci || (cj == ci && k < i)) ? 1 : 0;
+            }
+          }
+          s_rank[i] = (uint16_t)rank;
+          s_src[rank] = (uint16_t)i;
+          a.tord[g.atom_off + a0 + rank] = a0 + i;
+          a.nbc[g.atom_off + a0 + rank] = s_cnt0[i];
+        }
+        __syncthreads();
+        continue;
+      }
+      const int bn = b1 - b0;
+      // an item: half of the A or of the B neighbours of an atom, whole groups
+      for (int e = tid; e < 4 * bn; e += kListBlock) {
+        const bool isa = e < 2 * bn;
+        const int k = (e % (2 * bn)) % bn, half = (e % (2 * bn)) / bn;
+        // all masks present: columns in walk order; a batch: atoms in tile order
+        const int i = nbatch > 1 ? b0 + k : (int)s_src[k];
+        const int col = s_rank[i];
+        const int cb = s_cb[s_cell[i]];
+        const unsigned long long* M = s_mask + (i - b0) * words;
+        const int n = isa ? (s_cnt0[i] & 0xffff) : (s_cnt0[i] >> 16);
+        const int ng = (n + kGroup - 1) / kGroup;
+        const int g0 = half ? (ng + 1) / 2 : 0, g1 = half ? ng : (ng + 1) / 2;
+        if (g0 == g1) continue;
+        auto word = [&](int w) {   // (past the last word: not used)
+          w = min(w, words - 1);
+          const unsigned long long ta = s_ta[min(cb + w, kTileChunks - 1)];
+          return M[w] & (isa ? ta : ~ta);
+        };
+        // the half's first neighbour
+        int w = 0, skip = kGroup * g0;
+        unsigned long long m = word(0);
+        for (int c = __popcll(m); c <= skip; c = __popcll(m)) {
+          skip -= c;
+          m = word(++w);
+        }
+        for (; skip > 0; --skip) m &= m - 1ull;
+        unsigned long long ahead = word(w + 1);
+        auto next = [&]() -> uint32_t {   // the map entry of the segment's next neighbour
+          while (m == 0ull) {
+            m = ahead;
+            ++w;
+            ahead = word(w + 1);
+          }
+          const int bit = __ffsll((long long)m) - 1;
+          m &= m - 1ull;
+          return s_map[(cb + w) * kWave + bit];
+        };
+        if (lds) {
+          uint2* Pk = a.nbp + g.nb_off / kGroup + a0 + col;
+          for (int gs = g0; gs < g1; ++gs) {
+            uint32_t o[kGroup];
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) o[q] = kGroup * gs + q < n ? next() : fill;
+            Pk[(int64_t)(isa ? gs : G - 1 - gs) * g.npad] =
+                make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+          }
+        } else {
+          uint32_t* L = a.nbl + g.nb_off + a0 + col;
+          for (int q = kGroup * g0; q < min(kGroup * g1, n); ++q)
+            L[(int64_t)(isa ? q : a.max_nb - 1 - q) * g.npad] = global_entry((int)next());
+        }
+      }
+    }
+    return;
+  }
+  // A tile past the limits (or lists asked for as words): each atom scans its
+  // neighbouring cells itself, in FP64.
+  if (tid == 0) {
+    TileHdr h;
+    h.a0 = a0;
+    h.a1 = a1;
+    h.pad_ = 0;
+    h.halo = -1;
+    a.thdr[tix] = h;
+  }
+  for (int li = a0 + tid; li < a1; li += kListBlock) {
     const int64_t gi = g.atom_off + li;
     const double4 pi = P[li];
     const int tyi = (int)pi.w;
     double rl2[2];
-    float rl2f[2];
     for (int b = 0; b < 2; ++b) {
       const double rc = sqrt(a.pp[2 * tyi + b].rc2) + a.skin;
       rl2[b] = rc * rc;
-      rl2f[b] = (float)((rc + kListMargin) * (rc + kListMargin));
     }
-    const float pix = (float)(pi.x - ref.x), piy = (float)(pi.y - ref.y),
-                piz = (D == 3) ? (float)(pi.z - ref.z) : 0.0f;
     int c3[3];
     cell_of_pos<D>(bx, nc, pi, c3);
     uint32_t* L = a.nbl + g.nb_off + li;
@@ -343,48 +703,20 @@ __global__ __launch_bounds__(kBlock) void k_rb_list(RebuildArgs a) {
           if (cx < 0) { cx += nc[0]; ix = -1; }
           else if (cx >= nc[0]) { cx -= nc[0]; ix = 1; }
           const int code = (ix + 1) + 3 * (iy + 1) + 9 * (iz + 1);
-          const TileRun& rr = runs[run_of(c3[0], dx, dy, dz, nc[0])];
           double sh[3];
           box_shift(bx, ix, iy, iz, sh);
-          const double sx = sh[0], sy = sh[1], sz = sh[2];
           const int c = (cz2 * nc[1] + cy2) * nc[0] + cx;
-          const int jb = cs[c], je = cs[c + 1];
-          if (cand) {
-            // staged candidates, FP32 with the margin
-            const int hb = rr.off + (jb - rr.src);
-            for (int q = 0; q < je - jb; ++q) {
-              if (jb + q == li && code == 13) continue;
-              const int hc = hb + q;
-              const float fx = s_cx[hc] - pix, fy = s_cy[hc] - piy;
-              const float fz = (D == 3) ? s_cz[hc] - piz : 0.0f;
-              const int tj = s_ct[hc];
-              if (fx * fx + fy * fy + fz * fz < rl2f[tj]) {
-                atomicOr(&s_bits[hc >> 5], 1u << (hc & 31));
-                if (na + nb < a.max_nb) {
-                  const int row = (tj == 0) ? na : a.max_nb - 1 - nb;
-                  L[(int64_t)row * g.npad] = (uint32_t)hc;
-                } else {
-                  over = true;
-                }
-                if (tj == 0) ++na; else ++nb;
-              }
-            }
-            continue;
-          }
-          for (int j = jb; j < je; ++j) {
+          for (int j = cs[c]; j < cs[c + 1]; ++j) {
             if (j == li && code == 13) continue;
             const double4 pj = P[j];
-            const double ddx = (pj.x - pi.x) + sx;
-            const double ddy = (pj.y - pi.y) + sy;
-            const double ddz = (D == 3) ? (pj.z - pi.z) + sz : 0.0;
+            const double ddx = (pj.x - pi.x) + sh[0];
+            const double ddy = (pj.y - pi.y) + sh[1];
+            const double ddz = (D == 3) ? (pj.z - pi.z) + sh[2] : 0.0;
             const double r2 = ddx * ddx + ddy * ddy + ddz * ddz;
             if (r2 < rl2[(int)pj.w]) {
-              const uint32_t hc = (uint32_t)(rr.off + (j - rr.src));
-              const uint32_t ent = cand ? hc : ((uint32_t)j | ((uint32_t)code << kCodeShift));
-              if (cand) atomicOr(&s_bits[hc >> 5], 1u << (hc & 31));
               if (na + nb < a.max_nb) {
                 const int row = (pj.w == 0.0) ? na : a.max_nb - 1 - nb;
-                L[(int64_t)row * g.npad] = ent;
+                L[(int64_t)row * g.npad] = (uint32_t)j | ((uint32_t)code << kCodeShift);
               } else {
                 over = true;
               }
@@ -394,146 +726,9 @@ __global__ __launch_bounds__(kBlock) void k_rb_list(RebuildArgs a) {
         }
       }
     }
-    a.nbc[gi] = na | (nb << 16);
-    if (sortable) s_cnt0[li - a0] = na | (nb << 16);
-    // a tile with an LDS halo also needs the atom's A and B groups of the
-    // packed list to fit side by side
-    const int G = a.max_nb / kGroup;
-    if (cand && (na + kGroup - 1) / kGroup + (nb + kGroup - 1) / kGroup > G) over = true;
     if (over) atomicMax(a.overflow, na + nb);
-  }
-  __syncthreads();
-  // compact halo: the marked candidates, numbered in candidate order
-  __shared__ int s_max[2];
-  if (tid < kHaloWords) s_pre[tid] = __popc(s_bits[tid]);
-  if (tid == 0) {
-    s_max[0] = 0;
-    s_max[1] = 0;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int acc = 0;
-    for (int w = 0; w < kHaloWords; ++w) {
-      const int c = s_pre[w];
-      s_pre[w] = acc;
-      acc += c;
-    }
-    // LDS halo slot CAP - 1 is the force kernel's far fill slot
-    const bool lds = cand && acc < CAP;
-    s_lds = lds ? 1 : 0;
-    TileHdr h;
-    h.a0 = a0;
-    h.a1 = a1;
-    h.pad_ = 0;
-    h.halo = lds ? acc : -1;
-    a.thdr[tix] = h;
-  }
-  __syncthreads();
-  const bool lds = s_lds != 0;
-  // Walk order.  The consumers of a tile with an LDS halo walk its atoms by
-  // decreasing list length (ties by position), so the lanes of a wavefront
-  // have lists of similar length: tord[a0 + k] is the k-th atom, and its
-  // packed list and count sit in column a0 + k, so a wavefront still reads
-  // consecutive list words.  Other tiles keep their atoms in tile order.
-  __shared__ int s_src[kTileSort];
-  int32_t* nbc = a.nbc + g.atom_off;
-  for (int li = a0 + tid; li < a1; li += kBlock) {
-    const int ci = (nbc[li] & 0xffff) + (nbc[li] >> 16);
-    int rank = li - a0;
-    if (lds) {   // lds implies cand, so the tile is sortable and s_cnt0 is set
-      rank = 0;
-      for (int k = 0; k < nt; ++k) {
-        const int cj = (s_cnt0[k] & 0xffff) + (s_cnt0[k] >> 16);
-        rank += (cj > ci || (cj == ci && k < li - a0)) ? 1 : 0;
-      }
-      s_src[rank] = li - a0;
-    }
-    a.tord[g.atom_off + a0 + rank] = li;
-    atomicMax(&s_max[0], nbc[li] & 0xffff);
-    atomicMax(&s_max[1], nbc[li] >> 16);
-  }
-  if (lds) {
-    uint32_t* hx = a.hidx + tix * CAP;
-    for (int hc = tid; hc < ncand; hc += kBlock) {
-      const uint32_t w = s_bits[hc >> 5], bit = 1u << (hc & 31);
-      if (!(w & bit)) continue;
-      int r = 0;
-      while (r < kRuns - 1 && !(hc >= runs[r].off && hc < runs[r].off + runs[r].count)) ++r;
-      hx[s_pre[hc >> 5] + __popc(w & (bit - 1u))] =
-          (uint32_t)(runs[r].src + (hc - runs[r].off)) | ((uint32_t)runs[r].code << kCodeShift);
-    }
-  }
-  __syncthreads();
-  if (!cand) return;   // entries are already j | code, columns in tile order
-  if (!lds) {
-    // the compact halo does not fit: candidate numbers -> j | code in place,
-    // each atom's own rows only (its A and B rows never overlap)
-    for (int li = a0 + tid; li < a1; li += kBlock) {
-      const int c = nbc[li], na = c & 0xffff, nb = c >> 16;
-      uint32_t* L = a.nbl + g.nb_off + li;
-      for (int q = 0; q < na + nb; ++q) {
-        const int64_t row = q < na ? q : a.max_nb - 1 - (q - na);
-        const int hc = min((int)L[row * g.npad], ncand - 1);
-        int r = 0;
-        while (r < kRuns - 1 && !(hc >= runs[r].off && hc < runs[r].off + runs[r].count)) ++r;
-        L[row * g.npad] =
-            (uint32_t)(runs[r].src + (hc - runs[r].off)) | ((uint32_t)runs[r].code << kCodeShift);
-      }
-    }
-    return;
-  }
-  // Tile with an LDS halo: counts in walk order, then the packed list.  The
-  // word list keeps the scan's candidate numbers (original columns); each
-  // pass stages kGroup rows per group row of the tile's atoms in LDS and
-  // writes the groups of every atom in its walk-order column, entry =
-  // byte offset 8 h of the candidate's compact halo slot h, the last group
-  // of a segment padded with the far fill slot.
-  __shared__ int s_cnt[kTileSort];
-  uint32_t* s_stage = reinterpret_cast<uint32_t*>(s_work);   // the candidates are dead now
-  for (int k = tid; k < nt; k += kBlock) s_cnt[k] = s_cnt0[s_src[k]];
-  __syncthreads();
-  for (int k = tid; k < nt; k += kBlock) nbc[a0 + k] = s_cnt[k];
-  const int G = a.max_nb / kGroup;
-  const int rows_a = min(s_max[0], a.max_nb), rows_b = min(s_max[1], a.max_nb);
-  const int ga = (rows_a + kGroup - 1) / kGroup, gb = (rows_b + kGroup - 1) / kGroup;
-  const int ng = ga + gb;
-  const int ntc = max(nt, 1);
-  const int pg = max(1, kRowStage / (kGroup * ntc));
-  const uint32_t* Lt = a.nbl + g.nb_off + a0;
-  uint2* Pk = a.nbp + g.nb_off / kGroup + a0;
-  const uint32_t fill = 8u * (uint32_t)(CAP - 1);
-  auto halo_offset = [&](uint32_t hc) -> uint32_t {
-    hc = min(hc, (uint32_t)(ncand - 1));
-    const uint32_t w = s_bits[hc >> 5], bit = 1u << (hc & 31);
-    return 8u * (uint32_t)(s_pre[hc >> 5] + __popc(w & (bit - 1u)));
-  };
-  for (int g0 = 0; g0 < ng; g0 += pg) {
-    const int cnt = min(pg, ng - g0);
-    const int ne = cnt * kGroup * nt;
-    for (int e = tid; e < ne; e += kBlock) {
-      const int gq = g0 + e / (kGroup * nt), i = (e / nt) % kGroup, col = e % nt;
-      const bool isa = gq < ga;
-      const int q = kGroup * (isa ? gq : gq - ga) + i;
-      const bool ok = q < (isa ? rows_a : rows_b);
-      s_stage[e] = ok ? Lt[(int64_t)(isa ? q : a.max_nb - 1 - q) * g.npad + col] : 0u;
-    }
-    __syncthreads();
-    for (int e = tid; e < cnt * nt; e += kBlock) {
-      const int gq = g0 + e / nt, k = e % nt;
-      const bool isa = gq < ga;
-      const int gs = isa ? gq : gq - ga;   // group of the atom's segment
-      const int nk = isa ? (s_cnt[k] & 0xffff) : (s_cnt[k] >> 16);
-      if (kGroup * gs >= nk) continue;     // not one of this atom's groups
-      const int src = s_src[k];
-      const int base = (e / nt) * kGroup * nt;
-      uint32_t o[kGroup];
-#pragma unroll
-      for (int i = 0; i < kGroup; ++i)
-        o[i] = (kGroup * gs + i < nk) ? halo_offset(s_stage[base + i * nt + src]) : fill;
-      Pk[(int64_t)(isa ? gs : G - 1 - gs) * g.npad + k] =
-          make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
-    }
-    __syncthreads();
+    a.nbc[gi] = over ? 0 : na | (nb << 16);
+    a.tord[gi] = li;
   }
 }
 
@@ -573,11 +768,11 @@ void launch_rebuild(const RebuildArgs& a, int32_t max_cells_per_slot, hipStream_
   if (a.dim == 3) {
     hipLaunchKernelGGL(k_rb_perm<3>, dim3(a.nblk), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_rb_back<3>, dim3(a.nblk), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_rb_list<3>, dim3(a.ntile_blk), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_rb_list<3>, dim3(a.ntile_blk), dim3(kListBlock), 0, s, a);
   } else {
     hipLaunchKernelGGL(k_rb_perm<2>, dim3(a.nblk), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_rb_back<2>, dim3(a.nblk), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_rb_list<2>, dim3(a.ntile_blk), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_rb_list<2>, dim3(a.ntile_blk), dim3(kListBlock), 0, s, a);
   }
   hipLaunchKernelGGL(k_rb_done, dim3(a.nreps), dim3(256), 0, s, a);
 }

@@ -26,11 +26,7 @@ namespace aqs {
 
 constexpr int kRuns = 27;  // (dz, dy, part): 3 x 3 x 3 (2D uses dz = 0 only)
 constexpr int kTileSort = 1024;  // tiles up to this many atoms are walked by list length
-constexpr int kHaloWords = 128;  // candidate bitmap of the builder: tiles with more candidates
-                                 // (32 kHaloWords) keep global entries
-constexpr int kRowStage = 4096;  // list words the builder stages in LDS per pass (a pass holds
-                                 // whole groups: kGroup rows of up to kTileSort atoms)
-constexpr int kCandCap = 32 * kHaloWords;  // candidates a tile may have and still number them
+constexpr int kCandCap = 4096;   // candidates a tile may have and still number them
 // FP32 distance test of the list builder: pairs within rc_ab + skin + this
 // margin (sigma_AA) are kept, far more than the FP32 rounding of candidate
 // offsets within a few cells of the tile (below 1e-5); the extra pairs lie
@@ -88,13 +84,6 @@ __device__ __forceinline__ TileRun make_run(int r, int cx0, int cx1, int cy, int
   run.count = cs[c0 + xhi + 1] - run.src;
   run.code = (ix + 1) + 3 * (iy + 1) + 9 * (iz + 1);
   return run;
-}
-
-// Run of the neighbour cell (cx + dx, row + dy, dz) of a segment cell cx.
-__device__ __forceinline__ int run_of(int cx, int dx, int dy, int dz, int nc0) {
-  const int x = cx + dx;
-  const int part = x < 0 ? 0 : (x >= nc0 ? 2 : 1);
-  return ((dz + 1) * 3 + (dy + 1)) * 3 + part;
 }
 
 // Image code c = (ix+1) + 3 (iy+1) + 9 (iz+1); shift = H (ix, iy, iz).
