@@ -1210,9 +1210,6 @@ aqs_status aqs_create(const aqs_potential* pot, const aqs_fire_params* fire,
       q.sig2 = sig * sig;
       q.eps4 = 4.0 * eps;
       q.ucut = 4.0 * eps * (sc6 * sc6 - sc6);
-      q.sig6 = q.sig2 * q.sig2 * q.sig2;
-      q.c6 = 6.0 * q.eps4 * q.sig6;
-      q.c12 = 12.0 * q.eps4 * q.sig6 * q.sig6;
       c->rd[2 * a + b] = rc;      // descriptor cutoff = the pair cutoff
       c->rd2[2 * a + b] = rc * rc;
     }

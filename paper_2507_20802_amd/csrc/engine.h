@@ -184,7 +184,6 @@ struct CgState {
 
 struct PairParams {   // per type pair t = 2 ti + tj
   double rc2, sig2, eps4, ucut;
-  double sig6, c6, c12;   // s^6, 6 eps4 s^6, 12 eps4 s^12
 };
 
 struct FireParams {

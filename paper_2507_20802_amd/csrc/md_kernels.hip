@@ -82,10 +82,8 @@ __device__ __forceinline__ void block_reduce(double* v, const int* op, double (*
 // positions are gathered together while the next chunk's list entries are
 // already in flight, so one wavefront keeps 2 kChunk loads outstanding
 // instead of waiting on two dependent loads per pair.  1/r^2 is the hardware
-// reciprocal estimate (4.5e-8 relative) refined by one cubic step,
-// r <- r + r (e + e^2) with e = 1 - x r: e^3 is below 1e-21, so the result is
-// within 1 ulp of the rounded quotient, as after two Newton steps (maximum and
-// rms error the same on 2 10^5 arguments), with one operation less.
+// reciprocal estimate refined by two Newton-Raphson steps (r <- r (2 - x r)),
+// within 1 ulp of the rounded quotient.
 
 constexpr int kChunk = 2;
 // Fourth word of a buffer resource on gfx9-family GPUs (raw 32-bit data,
@@ -96,9 +94,11 @@ constexpr int kBufferFlags = 0x00020000;
 constexpr double kFarFill = 1.0e20;
 
 __device__ __forceinline__ double recip_nr(double x) {
-  const double r = __builtin_amdgcn_rcp(x);
-  const double e = fma(-x, r, 1.0);
-  return fma(r, fma(e, e, e), r);
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
 }
 
 // One pair term, branch-free: out-of-range pairs contribute exact zeros (the
@@ -106,10 +106,7 @@ __device__ __forceinline__ double recip_nr(double x) {
 // without divergence.  SAFE: the entry may be this atom itself or a stale
 // fill entry (distance 0), so it is masked by `live` and its 1/r^2 taken of
 // 1.0; otherwise every entry is another atom or the far fill slot, at a
-// positive distance.  U'(r)/r = (c6 - c12 / r^6) / r^8, c6 = 6 eps4 s^6 and c12 =
-// 12 eps4 s^12: the powers of s in the constants save an operation of the
-// chain r^2 -> force and one rounding or two (rms error 2.0 instead of 2.4
-// half-ulps of the larger term).
+// positive distance.  U'(r)/r = eps4 s6 (6 - 12 s6) / r^2 with s6 = (s/r)^6.
 template <int D, bool WE, bool SAFE>
 __device__ __forceinline__ void pair_term(bool live, double dx, double dy, double dz,
                                           const PairParams& q, double& fx, double& fy, double& fz,
@@ -117,14 +114,14 @@ __device__ __forceinline__ void pair_term(bool live, double dx, double dy, doubl
   const double r2 = (D == 3) ? dx * dx + dy * dy + dz * dz : dx * dx + dy * dy;
   const bool in = SAFE ? (live && (r2 < q.rc2)) : (r2 < q.rc2);
   const double inv = recip_nr(SAFE ? (in ? r2 : 1.0) : r2);
-  const double i3 = inv * inv * inv;
-  const double gv = (i3 * inv) * fma(-q.c12, i3, q.c6);
+  const double s2 = q.sig2 * inv;
+  const double s6 = s2 * s2 * s2;
+  const double gv = s6 * fma(-12.0 * q.eps4, s6, 6.0 * q.eps4) * inv;
   const double g = in ? gv : 0.0;
   fx += g * dx;
   fy += g * dy;
   if (D == 3) fz += g * dz;
   if (WE) {
-    const double s6 = q.sig6 * i3;
     e += in ? q.eps4 * (s6 * s6 - s6) - q.ucut : 0.0;
     w += g * dx * dy;
   }
