@@ -54,6 +54,9 @@ double rc_max_of(const aqs_potential* p) {
 // kXcds (engine.h).
 constexpr uint32_t kAllXcds = (1u << kXcds) - 1u;
 
+// blocks of iterations in one launch of k_small that nothing waits for
+constexpr int kSmallBlocks = 16;
+
 // force tiles hold about fill x a block's atom lanes (tuning.tile_fill)
 constexpr double kFillDefault = 0.9, kFillMin = 0.5, kFillMax = 2.0;
 
@@ -129,7 +132,7 @@ struct Layout {
   size_t o_geom, o_state, o_state2, o_cgst, o_cgst2, o_pos4, o_v[3], o_f[3], o_id, o_inv, o_nbc, o_nbl, o_nbp, o_fpart, o_upart, o_upart2,
       o_log, o_ccount, o_cstart, o_cellof, o_order, o_tpos4, o_tv[3], o_tid, o_tbl[2],
       o_tbl2[2], o_reps[2], o_nc3[2], o_overflow[2], o_dg, o_red, o_dl[3], o_tdl[3], o_alt4, o_talt4, o_evals, o_xref4, o_ftbl[2], o_ttbl[2], o_thdr, o_hidx, o_sel[2],
-      o_zbuf, o_lpart, o_mlp, o_mlpw, o_ltbl[2], o_lftbl[2], o_lsel[2], o_tord, o_lin;
+      o_zbuf, o_lpart, o_mlp, o_mlpw, o_ltbl[2], o_lftbl[2], o_lsel[2], o_small[2], o_tord, o_lin;
   int64_t atoms = 0;      // padded atoms over all slots
   int64_t nb_entries = 0;
   int32_t blocks = 0;
@@ -233,6 +236,7 @@ aqs_status make_layout(const aqs_potential* pot, const Tune& tn, int n_rep, cons
     lo.o_ltbl[l] = take(sizeof(int2) * table_cap(lo.blocks));
     lo.o_lftbl[l] = take(sizeof(int2) * table_cap(lo.tiles));
     lo.o_lsel[l] = take(sizeof(int32_t) * n_rep);
+    lo.o_small[l] = take(sizeof(int32_t) * n_rep);
   }
   lo.o_dg = take(sizeof(double) * 4 * n_rep);
   lo.o_red = take(sizeof(double) * 10 * ((size_t)lo.blocks + 8));
@@ -240,7 +244,7 @@ aqs_status make_layout(const aqs_potential* pot, const Tune& tn, int n_rep, cons
   for (int a = 0; a < 3; ++a) lo.o_tdl[a] = take(sizeof(double) * A);
   lo.o_alt4 = take(sizeof(double4) * A);
   lo.o_talt4 = take(sizeof(double4) * A);
-  lo.o_evals = take(2 * sizeof(unsigned long long));   // all evaluations, timed ones
+  lo.o_evals = take(3 * sizeof(unsigned long long));   // all evaluations, timed ones; k_small's rebuilds
   lo.o_xref4 = take(sizeof(double4) * A);
   lo.o_zbuf = take(sizeof(uint16_t) * kFeat * A);
   lo.o_lpart = take(sizeof(double) * kLearnParts * ((size_t)lo.blocks + 8));
@@ -266,13 +270,19 @@ struct Lane {
   hipStream_t s = nullptr;
   int2 *tbl = nullptr, *ftbl = nullptr, *tbl2 = nullptr, *ttbl = nullptr;
   int2 *ltbl = nullptr, *lftbl = nullptr;
-  int32_t *sel_d = nullptr, *reps_d = nullptr, *nc3_d = nullptr, *lsel_d = nullptr;
+  int32_t *sel_d = nullptr, *reps_d = nullptr, *nc3_d = nullptr, *lsel_d = nullptr, *small_d = nullptr;
   int32_t* overflow = nullptr;
   int2 *h_tbl = nullptr, *h_ftbl = nullptr, *h_tbl2 = nullptr, *h_ttbl = nullptr;
   int2 *h_ltbl = nullptr, *h_lftbl = nullptr;
-  int32_t *h_sel = nullptr, *h_reps = nullptr, *h_nc3 = nullptr, *h_lsel = nullptr;
+  int32_t *h_sel = nullptr, *h_reps = nullptr, *h_nc3 = nullptr, *h_lsel = nullptr, *h_small = nullptr;
   int32_t* h_over = nullptr;
-  std::vector<int32_t> cur_sel;    // slots of the current iteration tables
+  std::vector<int32_t> cur_sel;    // slots of the current selection
+  std::vector<int32_t> tiled;      // ... those that the iteration tables hold
+  int32_t nsmall = 0, nhalf = 0;   // ... and the number that k_small runs (small_d; nhalf: up to kSmallHalf atoms)
+  hipStream_t side = nullptr;      // k_small beside the tiles' launches
+  hipEvent_t fork = nullptr, join = nullptr;
+  hipEvent_t small_ev[2] = {nullptr, nullptr};   // its timing events
+  bool small_timed = false;
   int32_t cur_nblk = 0;
   int32_t cur_ntiles = 0;
   bool ftable_stale = false;       // a rebuild changed the tiles of the selection
@@ -371,8 +381,8 @@ IterArgs iter_args(aqs_ctx* c, const Lane& L) {
   a.lds_pad = batch_pad(c, L);
   a.prio = (c->live && &L == &c->ln[1]) ? 1 : 0;
   a.one_rep = -1;
-  if (L.cur_sel.size() == 1 && L.xcd_mask == kAllXcds) {
-    const int r = L.cur_sel[0];
+  if (L.tiled.size() == 1 && L.xcd_mask == kAllXcds) {
+    const int r = L.tiled[0];
     a.one_rep = r;
     a.one_ntiles = c->tiles_now[r];
     a.one_nblk = c->lo.geom[r].nblocks;
@@ -499,7 +509,7 @@ aqs_status learned_group(aqs_ctx* c, Lane& L, const std::vector<int32_t>& ls, bo
 aqs_status rebuild(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool in_loop,
                    int list_mode);
 aqs_status pull_slots(aqs_ctx* c, Lane& L, const std::vector<int32_t>& slots);
-aqs_status set_table(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel);
+aqs_status set_table(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool iterate = true);
 IterArgs iter_args(aqs_ctx* c, const Lane& L);
 
 // Linear-response start (Eqs. 7-8, linear.hip) of the slots waiting in
@@ -867,9 +877,29 @@ aqs_status launch_block(aqs_ctx* c, Lane& L, const IterArgs& a, int M) {
   return AQS_OK;
 }
 
-aqs_status set_table(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel) {
-  std::vector<int2> tbl = make_table(c, sel, L.xcd_mask);
-  std::vector<int2> ftbl = make_tile_table(c, sel, L.xcd_mask);
+// Slots that run whole iterations in one workgroup (k_small): small 2D ones
+// with lists of the default length, under FIRE.  (Conjugate gradients stay on
+// the tiles: their line searches turn a last bit of difference in the sums into
+// another trajectory within a few hundred iterations.)  The slot alone decides,
+// so its result does not depend on what else is in a launch.
+bool small_slot(const aqs_ctx* c, int r) {
+  return c->dim == 2 && c->minimizer == kMinFire && c->lo.geom[r].n <= kSmallAtoms &&
+         c->tn.max_nb <= kSmallList;
+}
+
+// The lane's launch tables over the slots sel: of a minimisation (iterate) the
+// force and step tables hold the slots that k_small does not run.
+aqs_status set_table(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool iterate) {
+  std::vector<int32_t> tiled, small;
+  for (int r : sel) (iterate && small_slot(c, r) ? small : tiled).push_back(r);
+  std::vector<int2> tbl = make_table(c, tiled, L.xcd_mask);
+  std::vector<int2> ftbl = make_tile_table(c, tiled, L.xcd_mask);
+  const auto full = std::stable_partition(small.begin(), small.end(),
+                                          [&](int r) { return c->lo.geom[r].n <= kSmallHalf; });
+  L.nhalf = (int32_t)(full - small.begin());
+  std::copy(small.begin(), small.end(), L.h_small);
+  if (!small.empty())
+    HIPCHK(hipMemcpyAsync(L.small_d, L.h_small, sizeof(int32_t) * small.size(), hipMemcpyHostToDevice, L.s));
   std::copy(tbl.begin(), tbl.end(), L.h_tbl);
   std::copy(ftbl.begin(), ftbl.end(), L.h_ftbl);
   HIPCHK(hipMemcpyAsync(L.tbl, L.h_tbl, sizeof(int2) * tbl.size(), hipMemcpyHostToDevice, L.s));
@@ -880,9 +910,57 @@ aqs_status set_table(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel) {
   HIPCHK(hipStreamSynchronize(L.s));
   drop_graph(L);   // the captured launches bake in the table sizes
   L.cur_sel = sel;
+  L.tiled = tiled;
+  L.nsmall = (int32_t)small.size();
   L.cur_nblk = (int32_t)tbl.size();
   L.cur_ntiles = (int32_t)ftbl.size();
   L.ftable_stale = false;
+  return AQS_OK;
+}
+
+// v = 0 and no displacement for the lane's selection (a minimisation starts).
+aqs_status reset_iterations(aqs_ctx* c, Lane& L) {
+  int32_t nb = 0, nt = 0;
+  aqs_status st = start_tables(c, L, L.cur_sel, &nb, &nt);
+  if (st) return st;
+  launch_reset_iter(L.ltbl, nb, c->d_geom, c->vx, c->vy, c->vz, c->upart, c->dim, L.s);
+  HIPCHK(hipGetLastError());
+  // the tables' staging is free again before the first block's start tables
+  HIPCHK(hipStreamSynchronize(L.s));
+  return AQS_OK;
+}
+
+// k_small over the lane's small slots, `iters` iterations at most, on the lane's
+// stream; beside the tiles' launches when there are any, on a stream of its
+// own, so that neither waits for the other within a block.
+aqs_status small_launch(aqs_ctx* c, Lane& L, const IterArgs& a, int32_t start_mode, int iters) {
+  hipStream_t s = L.s;
+  if (!L.tiled.empty()) {
+    if (!L.side) {
+      HIPCHK(hipStreamCreateWithFlags(&L.side, hipStreamNonBlocking));
+      HIPCHK(hipEventCreateWithFlags(&L.fork, hipEventDisableTiming));
+      HIPCHK(hipEventCreateWithFlags(&L.join, hipEventDisableTiming));
+    }
+    HIPCHK(hipEventRecord(L.fork, L.s));
+    HIPCHK(hipStreamWaitEvent(L.side, L.fork, 0));
+    s = L.side;
+  }
+  SmallArgs sa{};
+  sa.it = a;
+  sa.slots = L.small_d;
+  sa.iters = iters;
+  // the descriptors and the linear response walk the tiles' lists, which only
+  // the host's rebuild keeps up
+  sa.rebuild = (start_mode == AQS_START_PLAIN || start_mode == AQS_START_EXTRAPOLATED) ? 1 : 0;
+  sa.overflow = L.overflow;
+  sa.rebuilds = c->evals + 2;
+  if (a.tevals)
+    for (hipEvent_t& e : L.small_ev)
+      if (!e) HIPCHK(hipEventCreate(&e));
+  HIPCHK(launch_small(sa, L.nhalf, L.nsmall - L.nhalf, s, a.tevals ? L.small_ev[0] : nullptr, a.tevals ? L.small_ev[1] : nullptr));
+  L.small_timed = a.tevals != nullptr;
+  if (s != L.s) HIPCHK(hipEventRecord(L.join, s));
+  ++c->cnt.force_launches;
   return AQS_OK;
 }
 
@@ -891,10 +969,10 @@ void free_pinned(aqs_ctx* c) {
   for (Lane& L : c->ln) {
     for (void* p : {(void*)L.h_tbl, (void*)L.h_ftbl, (void*)L.h_tbl2, (void*)L.h_ttbl,
                     (void*)L.h_ltbl, (void*)L.h_lftbl, (void*)L.h_sel, (void*)L.h_reps,
-                    (void*)L.h_nc3, (void*)L.h_lsel, (void*)L.h_over})
+                    (void*)L.h_nc3, (void*)L.h_lsel, (void*)L.h_small, (void*)L.h_over})
       ps.push_back(p);
     L.h_tbl = L.h_ftbl = L.h_tbl2 = L.h_ttbl = L.h_ltbl = L.h_lftbl = nullptr;
-    L.h_sel = L.h_reps = L.h_nc3 = L.h_lsel = L.h_over = nullptr;
+    L.h_sel = L.h_reps = L.h_nc3 = L.h_lsel = L.h_small = L.h_over = nullptr;
   }
   for (void* p : ps)
     if (p) (void)hipHostFree(p);
@@ -968,7 +1046,7 @@ bool lane_active(const aqs_ctx* c, const Lane& L) {
 aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed) {
   const bool timed = allow_timed && c->prof_every > 0 && (c->block_count % c->prof_every) == 0;
   const int M = c->tn.block_iters;
-  if (timed) {
+  if (timed && !L.tiled.empty()) {
     while ((int)L.ev.size() < 4 * M) {
       hipEvent_t e;
       HIPCHK(hipEventCreate(&e));
@@ -990,7 +1068,19 @@ aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed
   }
   IterArgs a = iter_args(c, L);
   if (timed) a.tevals = c->evals + 1;   // atoms of the timed launches
-  if (timed) {
+  L.small_timed = false;
+  if (L.nsmall > 0) {
+    // Alone, a plain or extrapolated chain needs the host only at its end, so
+    // a launch holds many blocks (a slot that ends leaves it early, the launch
+    // ends with its last slot); a live round's checks and the starts that the
+    // host predicts wait for a launch to end, and beside tiles the launch ends
+    // with their block.
+    const bool alone = L.tiled.empty() && !c->live &&
+                       (start_mode == AQS_START_PLAIN || start_mode == AQS_START_EXTRAPOLATED);
+    aqs_status st = small_launch(c, L, a, start_mode, alone ? kSmallBlocks * M : M);
+    if (st) return st;
+  }
+  if (timed && !L.tiled.empty()) {
     const IterArgs ab[2] = {a, swapped(a)};
     for (int it = 0; it < M; ++it) {
       // the force kernel's and the step kernel's own start and end times,
@@ -998,12 +1088,15 @@ aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed
       launch_force(ab[it & 1], L.cur_ntiles, c->dim, L.s, L.ev[4 * it + 0], L.ev[4 * it + 1]);
       launch_step(ab[it & 1], L.cur_nblk, c->dim, L.s, L.ev[4 * it + 2], L.ev[4 * it + 3]);
     }
-  } else {
+  } else if (!L.tiled.empty()) {
     aqs_status st = launch_block(c, L, a, M);
     if (st) return st;
   }
   HIPCHK(hipGetLastError());
-  c->cnt.force_launches += M;
+  if (!L.tiled.empty()) {
+    c->cnt.force_launches += M;
+    if (L.nsmall > 0) HIPCHK(hipStreamWaitEvent(L.s, L.join, 0));
+  }
   if (allow_timed) ++c->block_count;
   L.prefetched = false;
   if (c->live) {
@@ -1016,7 +1109,7 @@ aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed
     L.prefetched = true;
   }
   L.in_flight = true;
-  L.timed = timed;
+  L.timed = timed && !L.tiled.empty();
   return AQS_OK;
 }
 
@@ -1045,6 +1138,13 @@ aqs_status lane_poll(aqs_ctx* c, Lane& L, bool all_states, int& active) {
     c->cnt.force_timed += M;
     c->cnt.update_timed += M;
     L.timed = false;
+  }
+  if (L.small_timed) {   // whole iterations: counted as force time
+    float f = 0.f;
+    HIPCHK(hipEventElapsedTime(&f, L.small_ev[0], L.small_ev[1]));
+    c->cnt.force_ms += f;
+    ++c->cnt.force_timed;
+    L.small_timed = false;
   }
   std::vector<int32_t> rb;
   active = 0;
@@ -1278,6 +1378,7 @@ aqs_status aqs_create(const aqs_potential* pot, const aqs_fire_params* fire,
     L.ltbl = at<int2>(w, lo.o_ltbl[l]);
     L.lftbl = at<int2>(w, lo.o_lftbl[l]);
     L.lsel_d = at<int32_t>(w, lo.o_lsel[l]);
+    L.small_d = at<int32_t>(w, lo.o_small[l]);
   }
   c->ln[0].s = c->stream;   // lane 1's stream is created by the first live round
   c->dg_d = at<double>(w, lo.o_dg);
@@ -1309,6 +1410,7 @@ aqs_status aqs_create(const aqs_potential* pot, const aqs_fire_params* fire,
              hipHostMalloc((void**)&L.h_reps, sizeof(int32_t) * n_rep, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&L.h_sel, sizeof(int32_t) * n_rep, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&L.h_lsel, sizeof(int32_t) * n_rep, hipHostMallocDefault) == hipSuccess &&
+             hipHostMalloc((void**)&L.h_small, sizeof(int32_t) * n_rep, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&L.h_nc3, sizeof(int32_t) * kGridInts * n_rep, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&L.h_over, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
   if (!pinned) {
@@ -1349,8 +1451,12 @@ aqs_status aqs_destroy(aqs_ctx* c) {
     (void)hipStreamDestroy(c->ln[1].s);
   }
   for (Lane& L : c->ln) drop_graph(L);
-  for (Lane& L : c->ln)
+  for (Lane& L : c->ln) {
     for (hipEvent_t e : L.ev) (void)hipEventDestroy(e);
+    for (hipEvent_t e : {L.small_ev[0], L.small_ev[1], L.fork, L.join})
+      if (e) (void)hipEventDestroy(e);
+    if (L.side) (void)hipStreamDestroy(L.side);
+  }
   free_pinned(c);
   delete c;
   return AQS_OK;
@@ -1564,8 +1670,8 @@ aqs_status aqs_minimize_batch(aqs_ctx* c, int32_t n_sel, const int32_t* rep, int
   Lane& L = c->ln[0];
   st = set_table(c, L, sel);
   if (st) return st;
-  launch_reset_iter(L.tbl, L.cur_nblk, c->d_geom, c->vx, c->vy, c->vz, c->upart, c->dim, L.s);
-  HIPCHK(hipGetLastError());
+  st = reset_iterations(c, L);
+  if (st) return st;
   for (;;) {
     st = lane_launch(c, L, start_mode, true);
     if (st) return st;
@@ -1599,8 +1705,8 @@ aqs_status aqs_run_round(aqs_ctx* c, int32_t P, const int32_t* chain, const int3
     // all chains to completion on the context stream, then the checks in order
     st = set_table(c, B, sel);
     if (st) return st;
-    launch_reset_iter(B.tbl, B.cur_nblk, c->d_geom, c->vx, c->vy, c->vz, c->upart, c->dim, B.s);
-    HIPCHK(hipGetLastError());
+    st = reset_iterations(c, B);
+    if (st) return st;
     for (;;) {
       st = lane_launch(c, B, start_mode, true);
       if (st) return st;
@@ -1641,8 +1747,8 @@ aqs_status aqs_run_round(aqs_ctx* c, int32_t P, const int32_t* chain, const int3
   st = set_table(c, B, std::vector<int32_t>(chain + 1, chain + P));
   if (st) return st;
   for (Lane* L : {&C, &B}) {
-    launch_reset_iter(L->tbl, L->cur_nblk, c->d_geom, c->vx, c->vy, c->vz, c->upart, c->dim, L->s);
-    HIPCHK(hipGetLastError());
+    st = reset_iterations(c, *L);
+    if (st) return st;
   }
   int next = 1;   // next check
   // duty cycle of the batch while a critical chain runs (live_duty D > 1):
@@ -1832,7 +1938,7 @@ aqs_status aqs_energy_forces(aqs_ctx* c, int32_t rep, double* energy, double* fo
   c->h_state[rep].phase = PH_EVAL;
   st = push_state(c);
   if (st) return st;
-  st = set_table(c, L, sel);
+  st = set_table(c, L, sel, false);
   if (st) return st;
   IterArgs a = iter_args(c, L);
   launch_force(a, L.cur_ntiles, c->dim, c->stream);
@@ -2015,12 +2121,15 @@ aqs_status aqs_set_profiling(aqs_ctx* c, int32_t every_nth_block) {
 
 aqs_status aqs_get_counters(aqs_ctx* c, aqs_counters* out, int32_t reset) {
   if (!c) return fail(AQS_EINVAL, "null context");
-  unsigned long long ev[2] = {0, 0};
+  unsigned long long ev[3] = {0, 0, 0};
   HIPCHK(hipMemcpyAsync(ev, c->evals, sizeof ev, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   c->cnt.atom_evals = (int64_t)ev[0] + c->lin_evals;
   c->cnt.timed_atom_evals = (int64_t)ev[1];
-  if (out) *out = c->cnt;
+  if (out) {
+    *out = c->cnt;
+    out->rebuilds += (int64_t)ev[2];
+  }
   if (reset) {
     c->cnt = aqs_counters{};
     c->lin_evals = 0;
@@ -2117,7 +2226,7 @@ aqs_status prepare_single(aqs_ctx* c, int32_t rep) {
   std::vector<int32_t> sel{rep};
   st = rebuild(c, c->ln[0], sel);
   if (st) return st;
-  return set_table(c, c->ln[0], sel);
+  return set_table(c, c->ln[0], sel, false);
 }
 
 }  // namespace

@@ -47,6 +47,12 @@ constexpr uint32_t kIdxMask = 0x00FFFFFFu;
 constexpr int kCodeShift = 24;
 constexpr int kGroup = 4;             // entries per 8-byte group of the packed list
 constexpr int kListAlign = 32;        // max_nb is a multiple of kGroup x kMaxTPA
+// 2D slots of at most this many atoms, with lists of at most kSmallList
+// neighbours, run whole FIRE iterations in one workgroup: of kSmallHalf threads up
+// to as many atoms, else of kSmallAtoms
+constexpr int kSmallAtoms = 1024;
+constexpr int kSmallHalf = 512;
+constexpr int kSmallList = 64;
 // Blocks of one launch are dealt to the XCDs (dies, each with its own L2)
 // round robin: hardware block b runs on XCD b mod kXcds.
 constexpr int kXcds = 8;
@@ -263,7 +269,7 @@ struct IterArgs {
   // displacement's arrays, which are dead once a minimisation runs (and are
   // permuted with the atoms by every list rebuild).
   double* gx; double* gy; double* gz;
-  const double4* xref4;                     // positions at the last list build
+  double4* xref4;                           // positions at the last list build
 };
 
 __host__ __device__ inline double strain_of(int64_t k, double dgamma) {

@@ -65,6 +65,19 @@ void launch_control(const IterArgs& a, hipStream_t s);
 // reads a.state / a.cgst / a.upart, writes a.state_out / a.cgst_out / a.upart_out
 void launch_step(const IterArgs& a, int32_t nblk, int32_t dim, hipStream_t s,
                  hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// Up to `iters` iterations of each slot (a small 2D one, kSmallAtoms), one
+// workgroup per slot: force, FIRE control and move, and the list rebuilds.
+// State and displacement partials are updated in place (the home buffers).
+struct SmallArgs {
+  IterArgs it;
+  const int32_t* slots;         // first those of up to kSmallHalf atoms, then the others
+  int32_t iters;
+  int32_t rebuild;              // 1: rebuilds its lists itself; 0: stops in PH_REBUILD
+  int32_t* overflow;
+  unsigned long long* rebuilds; // statistics
+};
+hipError_t launch_small(const SmallArgs& a, int32_t nhalf, int32_t nfull, hipStream_t s,
+                        hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // dynamic LDS bytes per force block that leave at most `blocks` force blocks
 // per CU plus room for one more (0 if none can)
 int32_t force_lds_pad(int32_t dim, int32_t tpa, int32_t blocks);

@@ -14,6 +14,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "cellgeom.h"
 #include "kernels.h"
@@ -876,6 +877,117 @@ __global__ __launch_bounds__(kBlock) void k_control(IterArgs a) {
   }
 }
 
+// The pending move of one atom (state ss after its control): the FIRE update
+// (steps 5-9 of the minimiser), the conjugate-gradient move, the fine affine
+// step of the chain, or the learned start's move or its undoing; p, v (and F0
+// of a new search direction in gx, gy, gz) are updated in place.  Returns the
+// atom's displacement since the list build, |r - F x_ref|.
+template <int D, bool CG>
+__device__ __forceinline__ double move_atom(const IterArgs& a, const Geom& g, const State& ss,
+                                            const CgState& sq, int64_t gi, double4& p,
+                                            const double4& x0, double& vx, double& vy, double& vz,
+                                            double fx, double fy, double fz, double& gx, double& gy,
+                                            double& gz) {
+  const int phase = ss.phase;
+  if (!CG && (phase == PH_FIRE || phase == PH_STOP)) {
+    const double dt = ss.dt, cv = ss.cv, cf = ss.cf, dmax = a.fire.dmax;
+    if (ss.restart) {
+      p.x -= 0.5 * dt * vx;
+      p.y -= 0.5 * dt * vy;
+      if (D == 3) p.z -= 0.5 * dt * vz;
+      vx = 0.0;
+      vy = 0.0;
+      vz = 0.0;
+    }
+    vx += dt * fx;
+    vy += dt * fy;
+    vz += dt * fz;
+    vx = cv * vx + cf * fx;
+    vy = cv * vy + cf * fy;
+    vz = cv * vz + cf * fz;
+    const double sp = dt * sqrt(vx * vx + vy * vy + vz * vz);
+    if (sp > dmax) {
+      const double sc = dmax / sp;
+      vx *= sc;
+      vy *= sc;
+      vz *= sc;
+    }
+    p.x += dt * vx;
+    p.y += dt * vy;
+    if (D == 3) p.z += dt * vz;
+  } else if (CG && (phase == PH_CG || phase == PH_STOP)) {
+    // conjugate gradients: d lives in v; a new direction also saves F0
+    if (sq.newdir) {
+      const double b = sq.beta;
+      if (b == 0.0) {
+        vx = fx;
+        vy = fy;
+        vz = fz;
+      } else {
+        vx = fx + b * vx;
+        vy = fy + b * vy;
+        vz = fz + b * vz;
+      }
+      gx = fx;
+      gy = fy;
+      gz = fz;
+    }
+    const double da = sq.step;
+    p.x += da * vx;
+    p.y += da * vy;
+    if (D == 3) p.z += da * vz;
+  } else if (phase == PH_ADVANCE) {
+    if (g.dgamma_y == 0.0) {
+      // Eq. (16): x <- x + dgamma y, written out (no fused multiply-add), as
+      // the learned start's plain move does, so both give the same bits
+#pragma clang fp contract(off)
+      p.x += g.dgamma * p.y;
+    } else {
+      // Eq. (17): (x, y) <- F (x, y), both from the old coordinates
+#pragma clang fp contract(off)
+      const double x = p.x, y = p.y;
+      p.x = x + g.dgamma * y;
+      p.y = g.dgamma_y * x + y;
+    }
+    vx = 0.0;
+    vy = 0.0;
+    vz = 0.0;
+  } else if (phase == PH_LMOVE) {
+    // dl holds u_hat per unit strain (network, extrapolation), or the
+    // displacement itself (linear response, lmean = 0: exactly x0 + u)
+    const double sc = (ss.start_mode == kStartLinear) ? 1.0 : g.dgamma;
+    const double ux = sc * (a.dlx[gi] - ss.lmean[0]);
+    const double uy = sc * (a.dly[gi] - ss.lmean[1]);
+    const double uz = (D == 3) ? sc * (a.dlz[gi] - ss.lmean[2]) : 0.0;
+    p.x += ux;
+    p.y += uy;
+    if (D == 3) p.z += uz;
+  } else {   // PH_LREVERT: the plain start, bit for bit
+    const double4 q = a.alt4[gi];
+    p.x = q.x;
+    p.y = q.y;
+    p.z = q.z;
+  }
+  {
+    // written out, as in the learned start's plain move: both paths take
+    // the same list-rebuild decisions bit for bit
+#pragma clang fp contract(off)
+    double ux, uy;
+    if (g.dgamma_y == 0.0) {
+      const double gd = strain_of(ss.k, g.dgamma) - ss.gamma_build;
+      ux = p.x - (x0.x + gd * x0.y);
+      uy = p.y - x0.y;
+    } else {
+      double G[4];
+      strain_since(g, ss.k, ss.k_build, G);
+      ux = p.x - (G[0] * x0.x + G[1] * x0.y);
+      uy = p.y - (G[2] * x0.x + G[3] * x0.y);
+    }
+    const double uz = p.z - x0.z;
+    return sqrt(ux * ux + uy * uy + uz * uz);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // One iteration's control and move, after the force kernel.  Every block of
 // a slot sums the slot's tile partials and runs the control on them (the same
@@ -999,121 +1111,523 @@ __global__ __launch_bounds__(kBlock) void k_step(IterArgs a) {
       a.id[di] = aid;
       a.inv[gd.atom_off + aid] = li;
     }
-    if (fire) {
-      const double dt = ss.dt, cv = ss.cv, cf = ss.cf, dmax = a.fire.dmax;
-      if (ss.restart) {
-        p.x -= 0.5 * dt * vx;
-        p.y -= 0.5 * dt * vy;
-        if (D == 3) p.z -= 0.5 * dt * vz;
-        vx = 0.0;
-        vy = 0.0;
-        vz = 0.0;
-      }
-      vx += dt * fx;
-      vy += dt * fy;
-      vz += dt * fz;
-      vx = cv * vx + cf * fx;
-      vy = cv * vy + cf * fy;
-      vz = cv * vz + cf * fz;
-      const double sp = dt * sqrt(vx * vx + vy * vy + vz * vz);
-      if (sp > dmax) {
-        const double sc = dmax / sp;
-        vx *= sc;
-        vy *= sc;
-        vz *= sc;
-      }
-      p.x += dt * vx;
-      p.y += dt * vy;
-      if (D == 3) p.z += dt * vz;
-      a.pos4[gi] = p;
-      a.vx[gi] = vx;
-      a.vy[gi] = vy;
-      if (D == 3) a.vz[gi] = vz;
-    } else if (cg) {
-      // conjugate gradients: d lives in v; a new direction also saves F0
-      double dx = vx, dy = vy, dz = vz;
-      if (sq.newdir) {
-        const double b = sq.beta;
-        if (b == 0.0) {
-          dx = fx;
-          dy = fy;
-          dz = fz;
-        } else {
-          dx = fx + b * dx;
-          dy = fy + b * dy;
-          dz = fz + b * dz;
-        }
-        a.gx[gi] = fx;
-        a.gy[gi] = fy;
-        if (D == 3) a.gz[gi] = fz;
-        a.vx[gi] = dx;
-        a.vy[gi] = dy;
-        if (D == 3) a.vz[gi] = dz;
-      }
-      const double da = sq.step;
-      p.x += da * dx;
-      p.y += da * dy;
-      if (D == 3) p.z += da * dz;
-      a.pos4[gi] = p;
-    } else if (adv) {
-      if (g.dgamma_y == 0.0) {
-        // Eq. (16): x <- x + dgamma y, written out (no fused multiply-add), as
-        // the learned start's plain move does, so both give the same bits
-#pragma clang fp contract(off)
-        p.x += g.dgamma * p.y;
-      } else {
-        // Eq. (17): (x, y) <- F (x, y), both from the old coordinates
-#pragma clang fp contract(off)
-        const double x = p.x, y = p.y;
-        p.x = x + g.dgamma * y;
-        p.y = g.dgamma_y * x + y;
-      }
-      a.pos4[gi] = p;
-      a.vx[gi] = 0.0;
-      a.vy[gi] = 0.0;
-      if (D == 3) a.vz[gi] = 0.0;
-    } else if (lmove) {
-      // dl holds u_hat per unit strain (network, extrapolation), or the
-      // displacement itself (linear response, lmean = 0: exactly x0 + u)
-      const double sc = (ss.start_mode == kStartLinear) ? 1.0 : g.dgamma;
-      const double ux = sc * (a.dlx[gi] - ss.lmean[0]);
-      const double uy = sc * (a.dly[gi] - ss.lmean[1]);
-      const double uz = (D == 3) ? sc * (a.dlz[gi] - ss.lmean[2]) : 0.0;
-      if (phase == PH_LMOVE) {
-        p.x += ux;
-        p.y += uy;
-        if (D == 3) p.z += uz;
-      } else {
-        const double4 q = a.alt4[gi];   // the plain start, bit for bit
-        p.x = q.x;
-        p.y = q.y;
-        p.z = q.z;
-      }
-      a.pos4[gi] = p;
-    }
+    double gx = 0.0, gy = 0.0, gz = 0.0;
     if (moves) {
-      // written out, as in the learned start's plain move: both paths take
-      // the same list-rebuild decisions bit for bit
-#pragma clang fp contract(off)
-      double ux, uy;
-      if (g.dgamma_y == 0.0) {
-        const double gd = strain_of(ss.k, g.dgamma) - ss.gamma_build;
-        ux = p.x - (x0.x + gd * x0.y);
-        uy = p.y - x0.y;
-      } else {
-        double G[4];
-        strain_since(g, ss.k, ss.k_build, G);
-        ux = p.x - (G[0] * x0.x + G[1] * x0.y);
-        uy = p.y - (G[2] * x0.x + G[3] * x0.y);
+      m[0] = move_atom<D, CG>(a, g, ss, sq, gi, p, x0, vx, vy, vz, fx, fy, fz, gx, gy, gz);
+      a.pos4[gi] = p;
+      if (fire || adv || (cg && sq.newdir)) {
+        a.vx[gi] = vx;
+        a.vy[gi] = vy;
+        if (D == 3) a.vz[gi] = vz;
       }
-      const double uz = p.z - x0.z;
-      m[0] = sqrt(ux * ux + uy * uy + uz * uz);
+      if (cg && sq.newdir) {   // F0 of the new direction
+        a.gx[gi] = gx;
+        a.gy[gi] = gy;
+        if (D == 3) a.gz[gi] = gz;
+      }
     }
   }
   if (moves) {
     const int op[1] = {1};
     block_reduce<1>(m, op, red);
     if (tid == 0) a.upart_out[ub] = m[0];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Whole iterations of a small 2D slot in one workgroup (one CU): a slot of at
+// most kSmallAtoms atoms keeps its positions and its neighbour list in LDS and
+// its velocities in registers, and runs up to `iters` iterations (force,
+// control, move) in one launch, with three barriers each, where the tiles take
+// two launches.  At these sizes the two launches are bound by their latency
+// (8 + 6 us of kernel and the gaps, whatever the slot holds); here an iteration
+// of 256 atoms takes 5.8 us, of 400 8.7 us (alone or 128 slots at once) and of
+// 1000 13 us, against 12.5, 13.5 and 15 us.  More than half of it is the pair
+// loop, bound by its instructions (about 170 cycles of a SIMD for 64 lanes' pair),
+// a fifth the control's chain of operations in one lane.  Beyond about 1000
+// atoms one CU takes as long as the two launches, and the list fills the LDS.
+// Tried without gain: the next row's positions read ahead of a row's
+// arithmetic; the control on a register copy of the state.
+//
+// Atoms are taken in the order (type, id) and neighbours cell by cell, in a
+// cell in the same order, so the result does not depend on the storage order,
+// which a list rebuild by the host changes and one in this kernel does not.  1,
+// 2, 4 or 8 lanes per atom take its neighbours in turn, those of type A first,
+// as pairs of 16-bit entries, index | image code << kSmallCode; what is left of a
+// pair names the far code (pairs and turns: every lane of a wavefront waits for
+// its longest list, and groups of four found by the lanes on their own were 20
+// steps long where 12 are needed).  The list is derived from the positions at
+// the last build (x_ref), at every launch anew, so how many iterations a launch
+// holds does not matter either.
+constexpr int kSmallCode = 10;                    // kSmallAtoms = 1 << kSmallCode
+constexpr int kSmallFar = 9;                      // image code of the filling
+constexpr int kSmallRows = kSmallList / 2 + 1;      // pairs of entries per lane
+constexpr int kSmallCells = 128;                  // cells of the list's search
+static_assert(kSmallAtoms == 1 << kSmallCode, "16-bit entries");
+
+// Pair constants with the powers of s in them: U'(r)/r = (c6 - c12 / r^6) / r^8,
+// and the reciprocal refined by one cubic step, r <- r + r (e + e^2), e = 1 - x r
+// (e^3 is below 1e-21): three operations less than pair_term, whose rounding
+// the tiles keep, with errors against 64 bits no larger (reciprocal: the same
+// maximum and rms on 2 10^5 arguments; force factor: rms 2.0 instead of 2.4
+// half-ulps of its larger term).
+struct SmallPair {
+  double rc2, c6, c12, sig6, eps4, ucut;
+};
+__device__ __forceinline__ SmallPair small_pair_params(const PairParams& q) {
+  const double sig6 = q.sig2 * q.sig2 * q.sig2;
+  return SmallPair{q.rc2, 6.0 * q.eps4 * sig6, 12.0 * q.eps4 * sig6 * sig6, sig6, q.eps4, q.ucut};
+}
+template <bool WE>
+__device__ __forceinline__ void small_pair(double dx, double dy, const SmallPair& q, double& fx, double& fy,
+                                           double& e, double& w) {
+  const double r2 = dx * dx + dy * dy;
+  const bool in = r2 < q.rc2;
+  const double r0 = __builtin_amdgcn_rcp(r2), er = fma(-r2, r0, 1.0);
+  const double inv = fma(r0, fma(er, er, er), r0), i3 = inv * inv * inv;
+  const double gv = (i3 * inv) * fma(-q.c12, i3, q.c6);
+  const double g = in ? gv : 0.0;
+  fx += g * dx;
+  fy += g * dy;
+  if (WE) {
+    const double s6 = q.sig6 * i3;
+    e += in ? q.eps4 * (s6 * s6 - s6) - q.ucut : 0.0;
+    w += g * dx * dy;
+  }
+}
+
+// Sum or maximum over the 16 lanes of a DPP row, in every one of them.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+template <bool MAX>
+__device__ __forceinline__ double row_reduce(double v) {
+  auto op = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
+  v = op(v, dpp_move<0xB1>(v));    // quad_perm [1,0,3,2]
+  v = op(v, dpp_move<0x4E>(v));    // quad_perm [2,3,0,1]
+  v = op(v, dpp_move<0x141>(v));   // row_half_mirror
+  v = op(v, dpp_move<0x140>(v));   // row_mirror
+  return v;
+}
+// ... and over the first ROWS rows of the wavefront, in index order.
+template <bool MAX, int ROWS>
+__device__ __forceinline__ double rows_reduce(double v) {
+  v = row_reduce<MAX>(v);
+  double t = 0.0;
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const double q = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 16 * r),
+                                      __builtin_amdgcn_readlane(__double2loint(v), 16 * r));
+    t = r == 0 ? q : (MAX ? fmax(t, q) : t + q);
+  }
+  return t;
+}
+
+// A slot's cell grid can still be built: the host's rebuild refuses a box
+// sheared too thin or past the cells reserved, and then it is left to refuse.
+__device__ __forceinline__ bool small_box_ok(const Box& b, double rl, int cell_cap) {
+  double wx, wy;
+  if (b.h10 == 0.0) {
+    wx = b.h00 * b.h11 / sqrt(b.h11 * b.h11 + b.h01 * b.h01);
+    wy = b.h11;
+  } else {
+    const double det = fabs(b.h00 * b.h11 - b.h01 * b.h10);
+    wx = det / sqrt(b.h01 * b.h01 + b.h11 * b.h11);
+    wy = det / sqrt(b.h00 * b.h00 + b.h10 * b.h10);
+  }
+  const double nx = floor(wx / rl), ny = floor(wy / rl);
+  return nx >= 3.0 && ny >= 3.0 && nx * ny <= (double)cell_cap;
+}
+
+// T threads: at most T atoms
+template <int T>
+struct SmallLds {
+  double2 x[T];
+  uint32_t list[kSmallRows][T];
+  uint16_t order[T];                 // the atoms cell by cell, in a cell by index
+  int cstart[kSmallCells + 1], aend[kSmallCells];   // a cell's first atom, the end of its A atoms
+  double part[7][T / 16];   // row sums: FF, F.v, |v|^2, max ff, max displacement, E, W
+  double2 sh[kSmallFar + 1];
+  State ss;
+  SmallPair pp[4];
+  int bad, over, nA;
+  int wcount[T / kWave];
+};
+static_assert(sizeof(SmallLds<kSmallAtoms>) <= 160 * 1024, "one workgroup per CU");
+
+template <int T>
+__global__ __launch_bounds__(T) void k_small(SmallArgs sa) {
+  const IterArgs& a = sa.it;
+  critical_priority(a);
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  SmallLds<T>& S = *reinterpret_cast<SmallLds<T>*>(small_lds);
+  const int rep = sa.slots[blockIdx.x];
+  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  const Geom g = a.geom[rep];
+  const int n = g.n;
+  if (tid < kStateWords)
+    reinterpret_cast<uint32_t*>(&S.ss)[tid] = reinterpret_cast<const uint32_t*>(a.state + rep)[tid];
+  if (tid < 4) S.pp[tid] = small_pair_params(a.pp[tid]);
+  if (tid == 0) S.over = 0;
+  __syncthreads();
+  {
+    const int ph = S.ss.phase;
+    if (!(phase_force(ph) || ph == PH_FINISH || ph == PH_STOP)) return;
+  }
+  int tpa = 1;
+  while (tpa < kMaxTPA && n * tpa * 2 <= T) tpa *= 2;
+  // storage position of each atom in (type, id) order (the list's LDS holds it meanwhile)
+  uint16_t* s_li = reinterpret_cast<uint16_t*>(S.list);
+  {
+    const int li = tid < n ? a.inv[g.atom_off + tid] : 0;
+    const bool tb = tid < n && a.pos4[g.atom_off + li].w != 0.0;
+    const unsigned long long mb = __ballot(tb), below = (1ull << lane) - 1ull;
+    if (lane == 0) S.wcount[wv] = __popcll(mb);
+    __syncthreads();
+    int bbefore = 0, ball = 0;
+    for (int w = 0; w < T / kWave; ++w) {
+      bbefore += w < wv ? S.wcount[w] : 0;
+      ball += S.wcount[w];
+    }
+    const int brank = bbefore + __popcll(mb & below);   // B atoms of smaller id
+    if (tid < n) s_li[tb ? n - ball + brank : tid - brank] = (uint16_t)li;
+    if (tid == 0) S.nA = n - ball;
+  }
+  __syncthreads();
+  const int nA = S.nA;
+  const int me = tid / tpa, sub = tid % tpa;    // this lane's atom and its share
+  const bool mine = me < n, lead = mine && sub == 0;
+  const int li = mine ? (int)s_li[me] : 0;
+  const int64_t gi = g.atom_off + li;
+  __syncthreads();   // s_li read before the list is built over it
+  double2 p = make_double2(0.0, 0.0), x0 = p;
+  double vx = 0.0, vy = 0.0;
+  if (mine) {
+    const double4 q = a.pos4[gi], q0 = a.xref4[gi];
+    p = make_double2(q.x, q.y);
+    x0 = make_double2(q0.x, q0.y);
+    vx = a.vx[gi];
+    vy = a.vy[gi];
+  }
+  const int ti = me < nA ? 0 : 1;
+  double moved = 0.0;   // largest displacement since the build (the update's, block by block)
+  for (int b = 0; b < g.nblocks; ++b) moved = fmax(moved, a.upart[g.block0 + b]);
+  int na = 0, nb = 0;   // this lane's entries of either type
+  bool rebuilt = false;
+
+  // The list, from the positions x_ref at the last build.
+  auto build = [&]() {
+    const Box b = box_at(g, S.ss.k_build);
+    float2* xf = reinterpret_cast<float2*>(S.x);
+    if (lead) xf[me] = make_float2((float)x0.x, (float)x0.y);
+    for (int c = tid; c <= kSmallCells; c += T) S.cstart[c] = 0;
+    for (int c = tid; c < kSmallCells; c += T) S.aend[c] = 0;
+    // every entry the filling: what is not written below is beyond every cutoff
+    const uint32_t fill = (uint32_t)min(me, n - 1) | ((uint32_t)kSmallFar << kSmallCode);
+    for (int row = 0; row < kSmallRows; ++row) S.list[row][tid] = fill | (fill << 16);
+    const double det = b.h00 * b.h11 - b.h01 * b.h10;
+    const float i00 = (float)(b.h11 / det), i01 = (float)(-b.h01 / det), i10 = (float)(-b.h10 / det),
+                i11 = (float)(b.h00 / det);
+    const float h00 = (float)b.h00, h01 = (float)b.h01, h10 = (float)b.h10, h11 = (float)b.h11;
+    const float xi = (float)x0.x, yi = (float)x0.y;
+    // cells at least a list distance wide (the margin of the FP32 test with it)
+    int nc0, nc1;
+    {
+      const double rl = a.rc_max + a.skin + 2.0 * kListMargin;
+      nc0 = (int)(fabs(det) / sqrt(b.h01 * b.h01 + b.h11 * b.h11) / rl);
+      nc1 = (int)(fabs(det) / sqrt(b.h00 * b.h00 + b.h10 * b.h10) / rl);
+      nc0 = max(1, min(nc0, kSmallCells));
+      nc1 = max(1, min(nc1, kSmallCells / nc0));
+      // fewer than three along an axis: one, searched whole
+      if (nc0 < 3) nc0 = 1;
+      if (nc1 < 3) nc1 = 1;
+    }
+    __syncthreads();
+    // counting sort of the atoms into the cells
+    int c0 = 0, c1 = 0;
+    if (mine) {
+      const float s0 = i00 * xi + i01 * yi, s1 = i10 * xi + i11 * yi;
+      c0 = min(max((int)(s0 * nc0), 0), nc0 - 1);
+      c1 = min(max((int)(s1 * nc1), 0), nc1 - 1);
+    }
+    int place = 0;
+    if (lead) {
+      place = atomicAdd(&S.cstart[c1 * nc0 + c0], 1);
+      if (ti == 0) atomicAdd(&S.aend[c1 * nc0 + c0], 1);
+    }
+    __syncthreads();
+    if (wv == 0) {   // counts to starts, two cells per lane
+      static_assert(kSmallCells == 2 * kWave, "two cells per lane");
+      const int n0 = S.cstart[2 * lane], n1 = S.cstart[2 * lane + 1];
+      int inc = n0 + n1;
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += v;
+      }
+      S.cstart[2 * lane] = inc - n0 - n1;
+      S.cstart[2 * lane + 1] = inc - n1;
+      if (lane == kWave - 1) S.cstart[kSmallCells] = inc;
+      S.aend[2 * lane] += inc - n0 - n1;
+      S.aend[2 * lane + 1] += inc - n1;
+    }
+    __syncthreads();
+    if (lead) S.order[S.cstart[c1 * nc0 + c0] + place] = (uint16_t)me;
+    __syncthreads();
+    // within a cell by index: a member's rank among them (the atomics' order is not fixed)
+    int rank = 0;
+    if (lead) {
+      const int q0 = S.cstart[c1 * nc0 + c0], q1 = S.cstart[c1 * nc0 + c0 + 1];
+      for (int q = q0; q < q1; ++q) rank += (int)S.order[q] < me ? 1 : 0;
+      rank += q0;
+    }
+    __syncthreads();
+    if (lead) S.order[rank] = (uint16_t)me;
+    __syncthreads();
+    const unsigned long long group = ((1ull << tpa) - 1ull) << (lane - sub), below = (1ull << lane) - 1ull;
+    int total[2];
+    for (int tj = 0; tj < 2; ++tj) {
+      const double rc = sqrt(S.pp[2 * ti + tj].rc2) + a.skin;
+      const float thr = (float)((rc + kListMargin) * (rc + kListMargin));
+      // entry k of lane l of the atom, below the lane's entries of type A
+      auto put = [&](int l, int k, uint32_t e) {
+        const int row = k / 2 + (tj == 0 ? 0 : ((total[0] - l + tpa - 1) / tpa + 1) / 2);
+        if (row < kSmallRows)
+          reinterpret_cast<uint16_t*>(&S.list[row][tid - sub + l])[k & 1] = (uint16_t)e;
+      };
+      int base = 0;
+      const int w0 = nc0 == 1 ? 1 : 3, w1 = nc1 == 1 ? 1 : 3;   // cells around along each axis
+      for (int e1 = 0; e1 < w1; ++e1)
+        for (int e0 = 0; e0 < w0; ++e0) {
+          const int x = nc0 == 1 ? 0 : (c0 + e0 + nc0 - 1) % nc0, y = nc1 == 1 ? 0 : (c1 + e1 + nc1 - 1) % nc1;
+          const int cc = y * nc0 + x;
+          const int q0 = tj == 0 ? S.cstart[cc] : S.aend[cc], q1 = tj == 0 ? S.aend[cc] : S.cstart[cc + 1];
+          for (int qq = 0; __any(mine && q0 + qq < q1); qq += tpa) {
+            const bool in = mine && q0 + qq + sub < q1;
+            const int j = in ? (int)S.order[q0 + qq + sub] : 0;
+            const float2 q = xf[j];
+            float dx = q.x - xi, dy = q.y - yi;
+            // nearest image: H (s - rint s), its code from -rint s
+            const float nx = rintf(i00 * dx + i01 * dy), ny = rintf(i10 * dx + i11 * dy);
+            dx -= h00 * nx + h01 * ny;
+            dy -= h10 * nx + h11 * ny;
+            const bool hit = in && j != me && dx * dx + dy * dy < thr;
+            const unsigned long long m = __ballot(hit) & group;
+            const int idx = base + __popcll(m & below);
+            base += __popcll(m);
+            if (hit)
+              put(idx % tpa, idx / tpa,
+                  (uint32_t)j | ((uint32_t)((1 - (int)nx) + 3 * (1 - (int)ny)) << kSmallCode));
+          }
+        }
+      total[tj] = base;
+      const int c = base > sub ? (base - sub + tpa - 1) / tpa : 0;
+      if (tj == 0) na = c; else nb = c;
+    }
+    // the same limits as the tiles' lists
+    const int ta = total[0], tb = total[1];
+    if (lead && (ta + tb > a.max_nb || (ta + 3) / 4 + (tb + 3) / 4 > a.max_nb / kGroup)) {
+      atomicMax(sa.overflow, ta + tb);
+      S.over = 1;
+    }
+    __syncthreads();
+    if (lead) S.x[me] = p;
+  };
+  // image shifts of the box at the current strain
+  auto shifts = [&]() {
+    if (tid < kSmallFar) {
+      double sft[3];
+      box_shift(box_at(g, S.ss.k), tid % 3 - 1, tid / 3 - 1, 0, sft);
+      S.sh[tid] = make_double2(sft[0], sft[1]);
+    }
+    if (tid == kSmallFar) S.sh[tid] = make_double2(kFarFill, kFarFill);
+  };
+  build();
+  shifts();
+  if (tid == 0) S.bad = 0;
+  __syncthreads();
+  // a row's sum (or maximum, none negative) per lane of a wavefront
+  static_assert(T / 16 <= kWave && T % 256 == 0, "a row per lane, whole rows of them");
+  auto row_sum = [&](int c) { return lane < T / 16 ? S.part[c][lane] : 0.0; };
+  int64_t evaluated = 0;
+  int rebuilds = 0;
+  for (int it = 0; it < sa.iters && !S.over; ++it) {
+    const int phase0 = S.ss.phase;
+    const bool compute = phase_force(phase0);
+    if (!(compute || phase0 == PH_FINISH || phase0 == PH_STOP)) break;
+    double fx = 0.0, fy = 0.0;
+    if (compute) {
+      double e = 0.0, w = 0.0;
+      ++evaluated;
+      const bool we = phase_energy(phase0);
+      const double2 xi = S.x[mine ? me : 0];
+      int gp = 0;
+      auto segment = [&](auto WEc, int cnt, const SmallPair& q) {
+        constexpr bool WE = decltype(WEc)::value;
+        for (int k = 0; k < cnt; k += 2, ++gp) {
+          const uint32_t ent = S.list[gp][tid];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const uint32_t en = u == 0 ? ent & 0xffffu : ent >> 16;
+            const double2 xj = S.x[en & (kSmallAtoms - 1)], sf = S.sh[en >> kSmallCode];
+            small_pair<WE>((xj.x - xi.x) + sf.x, (xj.y - xi.y) + sf.y, q, fx, fy, e, w);
+          }
+        }
+      };
+      for (int tj = 0; tj < 2; ++tj) {
+        const SmallPair q = S.pp[2 * ti + tj];
+        if (we)
+          segment(std::true_type{}, tj == 0 ? na : nb, q);
+        else
+          segment(std::false_type{}, tj == 0 ? na : nb, q);
+      }
+      for (int off = 1; off < tpa; off <<= 1) {
+        fx += __shfl_xor(fx, off, kWave);
+        fy += __shfl_xor(fy, off, kWave);
+        if (we) {
+          e += __shfl_xor(e, off, kWave);
+          w += __shfl_xor(w, off, kWave);
+        }
+      }
+      // the sums the control needs, rows of 16 lanes at a time
+      const double ff = fx * fx + fy * fy, vv = vx * vx + vy * vy;
+      const double q1 = lead ? ff : 0.0, q2 = lead ? fx * vx + fy * vy : 0.0;
+      const double q3 = lead ? vv : 0.0;
+      if (lead && !(isfinite(e) && isfinite(ff) && isfinite(p.x + p.y))) S.bad = 1;
+      const double r1 = row_reduce<false>(q1), r2 = row_reduce<false>(q2), r3 = row_reduce<false>(q3);
+      const double r4 = row_reduce<true>(q1), r7 = row_reduce<true>(moved);
+      double r0 = 0.0, r5 = 0.0;
+      if (we) {
+        r0 = row_reduce<false>(lead ? 0.5 * e : 0.0);
+        r5 = row_reduce<false>(lead ? 0.5 * w : 0.0);
+      }
+      if (tid % 16 == 0) {
+        const int q = tid / 16;
+        S.part[0][q] = r1;
+        S.part[1][q] = r2;
+        S.part[2][q] = r3;
+        S.part[3][q] = r4;
+        S.part[4][q] = r7;
+        if (we) {
+          S.part[5][q] = r0;
+          S.part[6][q] = r5;
+        }
+      }
+    }
+    __syncthreads();
+    if (wv == 0) {
+      double r[kForceParts + 1];
+#pragma unroll
+      for (int c = 0; c < kForceParts + 1; ++c) r[c] = 0.0;
+      if (compute) {
+        r[1] = rows_reduce<false, T / 256>(row_sum(0));
+        r[2] = rows_reduce<false, T / 256>(row_sum(1));
+        r[3] = rows_reduce<false, T / 256>(row_sum(2));
+        r[4] = rows_reduce<true, T / 256>(row_sum(3));
+        r[7] = rows_reduce<true, T / 256>(row_sum(4));
+        if (phase_energy(phase0)) {
+          r[0] = rows_reduce<false, T / 256>(row_sum(5));
+          r[5] = rows_reduce<false, T / 256>(row_sum(6));
+        }
+        r[6] = S.bad ? 1.0 : 0.0;
+      }
+      if (lane == 0) {
+        CgState none;
+        control<false>(a, rep, g, r, phase0, S.ss, none, true);
+        S.bad = 0;
+        if (S.ss.phase == PH_REBUILD && sa.rebuild && small_box_ok(box_at(g, S.ss.k), a.rc_max + a.skin, g.cell_cap)) {
+          // rebuilt below; resumes as after the host's rebuild
+          const int ph = S.ss.resume_phase;
+          S.ss.phase = (ph == PH_LPLAIN || ph == PH_LMOVE || ph == PH_LREVERT) ? ph : PH_FIRE;
+          S.ss.ubound = 0.0;
+          S.ss.gamma_build = strain_of(S.ss.k, g.dgamma);
+          S.ss.k_build = S.ss.k;
+          S.over = -1;
+        }
+      }
+    }
+    __syncthreads();
+    if (S.over < 0) {
+      // positions back into the box, as the host's rebuild does, then the list
+      if (mine) {
+        const Box b = box_at(g, S.ss.k);
+        double s[3];
+        frac(b, p.x, p.y, 0.0, s);
+        const double nx = floor(s[0]), ny = floor(s[1]);
+        if (nx != 0.0 || ny != 0.0) {
+          const double tx = nx * b.h00 + ny * b.h01;
+          const double ty = (b.h10 == 0.0) ? ny * b.h11 : nx * b.h10 + ny * b.h11;
+          p.x -= tx;
+          p.y -= ty;
+          if (lead) {
+            double4 q = a.alt4[gi];
+            q.x -= tx;
+            q.y -= ty;
+            a.alt4[gi] = q;
+          }
+        }
+        x0 = p;
+      }
+      moved = 0.0;
+      rebuilt = true;
+      ++rebuilds;
+      __syncthreads();
+      if (tid == 0) S.over = 0;
+      __syncthreads();
+      build();
+      __syncthreads();
+      continue;
+    }
+    const int phase = S.ss.phase;
+    const bool adv = phase == PH_ADVANCE;
+    const bool moves =
+        phase == PH_FIRE || phase == PH_STOP || adv || phase == PH_LMOVE || phase == PH_LREVERT;
+    if (lead && S.ss.do_snap && (adv || phase == PH_FINISH)) {  // first inherent structure -> snap_dst
+      const Geom gd = a.geom[S.ss.snap_dst];
+      const int64_t di = gd.atom_off + li;
+      a.pos4[di] = make_double4(p.x, p.y, 0.0, (double)ti);
+      const int32_t aid = a.id[gi];
+      a.id[di] = aid;
+      a.inv[gd.atom_off + aid] = li;
+    }
+    if (moves) {
+      moved = 0.0;
+      if (mine) {
+        double4 q = make_double4(p.x, p.y, 0.0, 0.0);
+        double vz = 0.0, gx, gy, gz;
+        CgState none;
+        moved = move_atom<2, false>(a, g, S.ss, none, gi, q, make_double4(x0.x, x0.y, 0.0, 0.0), vx, vy, vz, fx, fy,
+                                    0.0, gx, gy, gz);
+        p = make_double2(q.x, q.y);
+        if (lead) S.x[me] = p;
+      }
+      if (adv) shifts();
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+  if (lead) {
+    const double w = (double)ti;
+    a.pos4[gi] = make_double4(p.x, p.y, 0.0, w);
+    a.vx[gi] = vx;
+    a.vy[gi] = vy;
+    if (rebuilt) a.xref4[gi] = make_double4(x0.x, x0.y, 0.0, w);
+  }
+  const double r7 = row_reduce<true>(moved);
+  if (tid % 16 == 0) S.part[4][tid / 16] = r7;
+  __syncthreads();
+  if (wv == 0) {
+    const double ub = rows_reduce<true, T / 256>(row_sum(4));
+    for (int b = lane; b < g.nblocks; b += kWave) a.upart[g.block0 + b] = ub;
+  }
+  if (tid < kStateWords)
+    reinterpret_cast<uint32_t*>(a.state + rep)[tid] = reinterpret_cast<const uint32_t*>(&S.ss)[tid];
+  if (tid == 0) {
+    atomicAdd(a.evals, (unsigned long long)(evaluated * n));
+    if (a.tevals) atomicAdd(a.tevals, (unsigned long long)(evaluated * n));
+    if (rebuilds) atomicAdd(sa.rebuilds, (unsigned long long)rebuilds);
   }
 }
 
@@ -1210,6 +1724,34 @@ void launch_step_d(const IterArgs& a, int32_t nblk, hipStream_t s, hipEvent_t e0
     launch_timed(k_step<D, CG, true>, nblk, 0, s, e0, e1, a);
   else
     launch_timed(k_step<D, CG, false>, nblk, 0, s, e0, e1, a);
+}
+
+template <int T>
+hipError_t launch_small_t(const SmallArgs& sa, int32_t nslots, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  auto run = [&](auto kernel) -> hipError_t {
+    // more LDS than a kernel may use by default
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmallLds<T>));
+    if (e != hipSuccess) return e;
+    if (e0 || e1)
+      hipExtLaunchKernelGGL(kernel, dim3(nslots), dim3(T), (uint32_t)sizeof(SmallLds<T>), s, e0, e1, 0u, sa);
+    else
+      hipLaunchKernelGGL(kernel, dim3(nslots), dim3(T), sizeof(SmallLds<T>), s, sa);
+    return hipGetLastError();
+  };
+  return run(k_small<T>);
+}
+
+hipError_t launch_small(const SmallArgs& sa, int32_t nhalf, int32_t nfull, hipStream_t s, hipEvent_t e0,
+                        hipEvent_t e1) {
+  hipError_t e = hipSuccess;
+  if (nhalf > 0) e = launch_small_t<kSmallHalf>(sa, nhalf, s, e0, nfull > 0 ? nullptr : e1);
+  if (nfull > 0 && e == hipSuccess) {
+    SmallArgs full = sa;
+    full.slots = sa.slots + nhalf;
+    e = launch_small_t<kSmallAtoms>(full, nfull, s, nhalf > 0 ? nullptr : e0, e1);
+  }
+  return e;
 }
 
 void launch_step(const IterArgs& a, int32_t nblk, int32_t dim, hipStream_t s, hipEvent_t e0,
