@@ -569,11 +569,24 @@ __global__ __launch_bounds__(kBlock) void k_colsum(const float* x, int64_t n, in
   double s = 0.0, cnt = 0.0;
   if (col < C) {
     const double mu = mean ? mean[col] : 0.0;
-    for (int64_t r = r0 + rg; r < r1; r += ngr) {
-      if (keep && !keep[r]) continue;
-      const double v = (double)x[r * ld + col];
-      s += mean ? (v - mu) * (v - mu) : v;
-      cnt += 1.0;
+    // rows in their order, kRowsAhead of them loaded at a time
+    constexpr int kRowsAhead = 8;
+    for (int64_t r = r0 + rg; r < r1; r += kRowsAhead * ngr) {
+      float v[kRowsAhead];
+      bool in[kRowsAhead];
+#pragma unroll
+      for (int k = 0; k < kRowsAhead; ++k) {
+        const int64_t q = r + (int64_t)k * ngr;
+        in[k] = q < r1 && (!keep || keep[q]);
+        v[k] = q < r1 ? x[q * ld + col] : 0.0f;
+      }
+#pragma unroll
+      for (int k = 0; k < kRowsAhead; ++k)
+        if (in[k]) {
+          const double d = (double)v[k];
+          s += mean ? (d - mu) * (d - mu) : d;
+          cnt += 1.0;
+        }
     }
   }
   __shared__ double sh[kBlock], shc[kBlock];
@@ -598,10 +611,24 @@ __global__ void k_colfin(const double* part, int nblk, int C, int pass, double* 
                          double* std64, float* fmean, float* fstd) {
   const int c = threadIdx.x;
   if (c >= C) return;
+  // kAhead chunks in flight at once, summed in chunk order: the launch is one
+  // wavefront's chain of memory round trips (30 us of them one chunk a trip)
+  constexpr int kAhead = 32;
   double s = 0.0, cnt = 0.0;
-  for (int b = 0; b < nblk; ++b) {
-    s += part[(int64_t)b * 64 + c];
-    cnt += part[(int64_t)kStatBlocks * 64 + b];
+  for (int b0 = 0; b0 < nblk; b0 += kAhead) {
+    double v[kAhead], n[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const int b = min(b0 + k, nblk - 1);
+      v[k] = part[(int64_t)b * 64 + c];
+      n[k] = part[(int64_t)kStatBlocks * 64 + b];
+    }
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      if (b0 + k < nblk) {
+        s += v[k];
+        cnt += n[k];
+      }
   }
   if (pass == 0) {
     mean64[c] = s / cnt;
@@ -639,10 +666,16 @@ __global__ __launch_bounds__(kBlock) void k_tprep(TrainArgs a) {
 constexpr int kS64 = 64 + 8;    // stride of [feature][row] buffers (64 rows)
 constexpr int kGS = 32 + 8;     // stride of the output-error rows
 
-// Forward and backward of 64 samples (4 wavefronts x 16 rows), then this
-// block's share of every gradient: dW = X^T dY over its 64 rows on the
-// matrix cores, bias gradients as FP64 sums; written to part[blockIdx.x].
-__global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
+// Forward and backward of 64 samples, then this block's share of every
+// gradient: dW = X^T dY over its 64 rows on the matrix cores, bias gradients
+// as FP64 sums; written to part[blockIdx.x].  16 wavefronts: four groups of 16
+// rows, each shared by four wavefronts that take two of the eight 16-column
+// tiles of every layer (the weights' tiles and the activations' round trips
+// through LDS are a chain of latencies; with four wavefronts taking all eight
+// tiles one after another a batch of 4096 took 30.5 us, now 23.4).
+constexpr int kTfbWaves = 16;
+constexpr int kTfbTiles = 8 / (kTfbWaves / 4);   // column tiles of a wavefront
+__global__ __launch_bounds__(64 * kTfbWaves) void k_tfb(TrainArgs a) {
   const MlpDev* M = a.mlp;
   __shared__ __attribute__((aligned(16))) uint16_t zT[kFeat][kS64];
   __shared__ __attribute__((aligned(16))) uint16_t h1r[64][kHS];
@@ -655,7 +688,9 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t d1T[kHid][kS64];
   __shared__ double bsum[4][2 * kHid + 4];
   __shared__ double lsum[4];
-  const int tid = threadIdx.x, w = tid / 64, l = tid % 64;
+  const int tid = threadIdx.x, l = tid % 64;
+  const int w = (tid / 64) % 4;                       // group of 16 rows
+  const int share = tid / 256, n0t = share * kTfbTiles;  // this wavefront's column tiles of it
   const int lr = l & 15, lg = l >> 4, lk = 8 * lg;
   const int rw = w * 16;                              // first row of this wave
   const int rowA = blockIdx.x * 64 + rw + lr;         // batch row of this lane's A fragment
@@ -670,19 +705,22 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
       q1 = *reinterpret_cast<const uint4*>(a.z + sA * kFeat + lk + 32);
     }
     const uint32_t qa[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+    if (share == 0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      zT[lk + 2 * j][rw + lr] = (uint16_t)(qa[j] & 0xffffu);
-      zT[lk + 2 * j + 1][rw + lr] = (uint16_t)(qa[j] >> 16);
-      zT[32 + lk + 2 * j][rw + lr] = (uint16_t)(qa[4 + j] & 0xffffu);
-      zT[32 + lk + 2 * j + 1][rw + lr] = (uint16_t)(qa[4 + j] >> 16);
+      for (int j = 0; j < 4; ++j) {
+        zT[lk + 2 * j][rw + lr] = (uint16_t)(qa[j] & 0xffffu);
+        zT[lk + 2 * j + 1][rw + lr] = (uint16_t)(qa[j] >> 16);
+        zT[32 + lk + 2 * j][rw + lr] = (uint16_t)(qa[4 + j] & 0xffffu);
+        zT[32 + lk + 2 * j + 1][rw + lr] = (uint16_t)(qa[4 + j] >> 16);
+      }
     }
     z0 = *reinterpret_cast<const bf16x8*>(&q0);
     z1 = *reinterpret_cast<const bf16x8*>(&q1);
   }
-  f32x4 a1[8], a2[8];
+  f32x4 a1[kTfbTiles], a2[kTfbTiles];
 #pragma unroll
-  for (int nt = 0; nt < 8; ++nt) {
+  for (int t = 0; t < kTfbTiles; ++t) {
+    const int nt = n0t + t;
     const uint16_t* wb = M->w1t + (nt * 16 + lr) * kFeat + lk;
     f32x4 acc = mma(z0, ld8(wb), zero4());
     acc = mma(z1, ld8(wb + 32), acc);
@@ -690,8 +728,8 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
     const float b = M->b1[col];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      a1[nt][i] = acc[i] + b;
-      const uint16_t h = f2bf(silu(a1[nt][i]));
+      a1[t][i] = acc[i] + b;
+      const uint16_t h = f2bf(silu(a1[t][i]));
       h1r[rw + 4 * lg + i][col] = h;
       h1T[col][rw + 4 * lg + i] = h;
     }
@@ -702,7 +740,8 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) hA[kk] = ld8(&h1r[rw + lr][kk * 32 + lk]);
 #pragma unroll
-  for (int nt = 0; nt < 8; ++nt) {
+  for (int t = 0; t < kTfbTiles; ++t) {
+    const int nt = n0t + t;
     f32x4 acc = zero4();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -711,58 +750,61 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
     const float b = M->b2[col];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      a2[nt][i] = acc[i] + b;
-      const uint16_t h = f2bf(silu(a2[nt][i]));
+      a2[t][i] = acc[i] + b;
+      const uint16_t h = f2bf(silu(a2[t][i]));
       h2r[rw + 4 * lg + i][col] = h;
       h2T[col][rw + 4 * lg + i] = h;
     }
   }
   __syncthreads();
-  // ---- layer 3 and the output error g = clip(y - t) / (rows d)
+  // ---- layer 3 (one wavefront of each group) and the output error g = clip(y - t) / (rows d)
+  if (share == 0) {
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) hA[kk] = ld8(&h2r[rw + lr][kk * 32 + lk]);
-  f32x4 y = zero4();
+    for (int kk = 0; kk < 4; ++kk) hA[kk] = ld8(&h2r[rw + lr][kk * 32 + lk]);
+    f32x4 y = zero4();
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) y = mma(hA[kk], ld8(M->w3t + lr * kHid + kk * 32 + lk), y);
-  const int c = lr;
-  const float bd = (float)(a.rows * a.dim);
-  double gsum = 0.0, lossw = 0.0;
+    for (int kk = 0; kk < 4; ++kk) y = mma(hA[kk], ld8(M->w3t + lr * kHid + kk * 32 + lk), y);
+    const int c = lr;
+    const float bd = (float)(a.rows * a.dim);
+    double gsum = 0.0, lossw = 0.0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = blockIdx.x * 64 + rw + 4 * lg + i;
-    float gv = 0.0f;
-    if (c < a.dim && row < a.rows && (!a.keep || a.keep[a.order[a.b0 + row]])) {
-      const int64_t s = a.order[a.b0 + row];
-      const float e = (y[i] + M->b3[c]) - a.t[s * 4 + c];
-      const float ae = fabsf(e);
-      lossw += (ae <= a.delta) ? 0.5 * (double)e * (double)e
-                               : (double)a.delta * ((double)ae - 0.5 * (double)a.delta);
-      gv = fminf(fmaxf(e, -a.delta), a.delta) / bd;
+    for (int i = 0; i < 4; ++i) {
+      const int row = blockIdx.x * 64 + rw + 4 * lg + i;
+      float gv = 0.0f;
+      if (c < a.dim && row < a.rows && (!a.keep || a.keep[a.order[a.b0 + row]])) {
+        const int64_t s = a.order[a.b0 + row];
+        const float e = (y[i] + M->b3[c]) - a.t[s * 4 + c];
+        const float ae = fabsf(e);
+        lossw += (ae <= a.delta) ? 0.5 * (double)e * (double)e
+                                 : (double)a.delta * ((double)ae - 0.5 * (double)a.delta);
+        gv = fminf(fmaxf(e, -a.delta), a.delta) / bd;
+      }
+      gsum += (double)gv;
+      const uint16_t gb = f2bf(gv);
+      gr[rw + 4 * lg + i][c] = gb;
+      gr[rw + 4 * lg + i][16 + c] = 0;
+      gT[c][rw + 4 * lg + i] = gb;
     }
-    gsum += (double)gv;
-    const uint16_t gb = f2bf(gv);
-    gr[rw + 4 * lg + i][c] = gb;
-    gr[rw + 4 * lg + i][16 + c] = 0;
-    gT[c][rw + 4 * lg + i] = gb;
+    // bias gradient of layer 3 (columns c) and the loss: fixed-order sums
+    gsum += __shfl_xor(gsum, 16, 64);
+    gsum += __shfl_xor(gsum, 32, 64);
+    for (int o = 32; o > 0; o >>= 1) lossw += __shfl_xor(lossw, o, 64);
+    if (l < 4) bsum[w][2 * kHid + l] = gsum;
+    if (l == 0) lsum[w] = lossw;
   }
-  // bias gradient of layer 3 (columns c) and the loss: fixed-order sums
-  gsum += __shfl_xor(gsum, 16, 64);
-  gsum += __shfl_xor(gsum, 32, 64);
-  for (int o = 32; o > 0; o >>= 1) lossw += __shfl_xor(lossw, o, 64);
-  if (l < 4) bsum[w][2 * kHid + l] = gsum;
-  if (l == 0) lsum[w] = lossw;
   __syncthreads();
   // ---- dL/dh2 = g W3^T, dL/da2 = dL/dh2 silu'(a2)
   {
     const bf16x8 gA = ld8(&gr[rw + lr][lk]);
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) {
+    for (int t = 0; t < kTfbTiles; ++t) {
+      const int nt = n0t + t;
       const f32x4 dh = mma(gA, ld8(M->w3n + (nt * 16 + lr) * 32 + lk), zero4());
       const int col = nt * 16 + lr;
       double bs = 0.0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float dz = dh[i] * dsilu(a2[nt][i]);
+        const float dz = dh[i] * dsilu(a2[t][i]);
         bs += (double)dz;
         const uint16_t hb = f2bf(dz);
         h2r[rw + 4 * lg + i][col] = hb;
@@ -778,7 +820,8 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) hA[kk] = ld8(&h2r[rw + lr][kk * 32 + lk]);
 #pragma unroll
-  for (int nt = 0; nt < 8; ++nt) {
+  for (int t = 0; t < kTfbTiles; ++t) {
+    const int nt = n0t + t;
     f32x4 dh = zero4();
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -787,7 +830,7 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
     double bs = 0.0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float dz = dh[i] * dsilu(a1[nt][i]);
+      const float dz = dh[i] * dsilu(a1[t][i]);
       bs += (double)dz;
       d1T[col][rw + 4 * lg + i] = f2bf(dz);
     }
@@ -799,7 +842,7 @@ __global__ __launch_bounds__(kBlock) void k_tfb(TrainArgs a) {
   // ---- weight gradients over the block's 64 rows (K = 64: two steps)
   float* P = a.part + (int64_t)blockIdx.x * (kNumParams + 1);
   // 104 output tiles: dW3 (8: 128 x 16), dW2 (64: 128 x 128), dW1 (32: 64 x 128)
-  for (int tt = w; tt < 104; tt += 4) {
+  for (int tt = tid / 64; tt < 104; tt += kTfbWaves) {
     const uint16_t *A, *B;
     int m0, n0, off, ldo, nmax;
     if (tt < 8) {
@@ -863,19 +906,35 @@ __device__ __forceinline__ void sync_param(int p, float wv, MlpDev* M) {
   }
 }
 
-// Gradient = partials summed in block order; then Adam (FP32, the order of
-// operations of Kingma and Ba's Algorithm 1) and the BF16 copies.  With
+// Gradient = partials summed in block order (6 us a launch at 64 partials; 29
+// with one partial a round trip, the loss before it in thread 0); then Adam
+// (FP32, the order of operations of Kingma and Ba's Algorithm 1) and the BF16
+// copies.  With
 // grad_out set, only the gradient is written.
 __global__ __launch_bounds__(kBlock) void k_tadam(TrainArgs a) {
   const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p == 0 && a.loss_acc) {
-    double s = 0.0;
-    for (int b = 0; b < a.nblk; ++b) s += (double)a.part[(int64_t)b * (kNumParams + 1) + kNumParams];
-    *a.loss_acc += s / ((double)a.rows * (double)a.dim);
-  }
-  if (p >= kNumParams) return;
+  // thread kNumParams sums the loss
+  if (p > kNumParams || (p == kNumParams && !a.loss_acc)) return;
+  // kPartsAhead partials in flight at once, added in block order
+  constexpr int kPartsAhead = 16;
+  double loss = 0.0;
   float g = 0.0f;
-  for (int b = 0; b < a.nblk; ++b) g += a.part[(int64_t)b * (kNumParams + 1) + p];
+  for (int b0 = 0; b0 < a.nblk; b0 += kPartsAhead) {
+    float v[kPartsAhead];
+#pragma unroll
+    for (int k = 0; k < kPartsAhead; ++k)
+      v[k] = a.part[(int64_t)min(b0 + k, a.nblk - 1) * (kNumParams + 1) + p];
+#pragma unroll
+    for (int k = 0; k < kPartsAhead; ++k)
+      if (b0 + k < a.nblk) {
+        g += v[k];
+        loss += (double)v[k];
+      }
+  }
+  if (p == kNumParams) {
+    *a.loss_acc += loss / ((double)a.rows * (double)a.dim);
+    return;
+  }
   if (a.grad_out) {
     a.grad_out[p] = g;
     return;
@@ -991,11 +1050,11 @@ void launch_train_prep(const TrainArgs& a, hipStream_t s) {
 }
 
 void launch_train_batch(const TrainArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_tfb, dim3(a.nblk), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_tfb, dim3(a.nblk), dim3(64 * kTfbWaves), 0, s, a);
 }
 
 void launch_train_update(const TrainArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_tadam, dim3((kNumParams + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_tadam, dim3((kNumParams + 1 + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
 }
 
 void launch_mlp_sync(const float* master, MlpDev* mlp, hipStream_t s) {
