@@ -54,6 +54,8 @@ double rc_max_of(const aqs_potential* p) {
 // kXcds (engine.h).
 constexpr uint32_t kAllXcds = (1u << kXcds) - 1u;
 
+// pinned staging kept for many small slots (one slot always fits)
+constexpr size_t kStageBytes = size_t(4) << 20;
 // blocks of iterations in one launch of k_small that nothing waits for
 constexpr int kSmallBlocks = 16;
 
@@ -346,6 +348,13 @@ struct aqs_ctx {
   double rd[4], rd2[4], dirs[16][3];
   // host mirrors
   State* h_state = nullptr;  // pinned
+  // h_state holds what the device does: set by a whole read-back or write, off
+  // once a kernel that writes states is launched
+  bool synced = false;
+  // pinned staging of atoms, a ring without wrap: what is taken stays in use
+  // until the context stream has been waited for
+  char* stage = nullptr;
+  size_t stage_cap = 0, stage_off = 0;
   std::vector<char> loaded, dirty;
   std::vector<int32_t> tiles_now;  // force tiles of each slot's current grid
   // driver lanes (pinned staging: one use per synchronisation of the lane)
@@ -685,11 +694,49 @@ std::vector<int2> make_tile_table(aqs_ctx* c, const std::vector<int32_t>& sel, u
 // Host copy of every slot's state (and lane 0's overflow flag), on the
 // context stream.
 aqs_status pull_state(aqs_ctx* c) {
+  if (c->synced) return AQS_OK;
   Lane& L = c->ln[0];
   HIPCHK(hipMemcpyAsync(c->h_state, c->d_state, sizeof(State) * c->n_rep, hipMemcpyDeviceToHost,
                         L.s));
   HIPCHK(hipMemcpyAsync(L.h_over, L.overflow, sizeof(int32_t), hipMemcpyDeviceToHost, L.s));
   HIPCHK(hipStreamSynchronize(L.s));
+  c->stage_off = 0;
+  c->synced = true;
+  return AQS_OK;
+}
+
+// bytes of pinned staging, free until the context stream is next waited for
+aqs_status stage_take(aqs_ctx* c, size_t bytes, void** out) {
+  bytes = align_up(bytes, 64);
+  if (!c->stage) {
+    size_t most = 0;
+    for (const Geom& g : c->lo.geom) most = std::max(most, (size_t)g.n * (8 * c->dim + 1) + 64);
+    c->stage_cap = align_up(std::max(most, std::min(kStageBytes, most * c->n_rep)), 64);
+    HIPCHK(hipHostMalloc((void**)&c->stage, c->stage_cap, hipHostMallocDefault));
+    c->stage_off = 0;
+  }
+  if (c->stage_off + bytes > c->stage_cap) {
+    HIPCHK(hipStreamSynchronize(c->stream));
+    c->stage_off = 0;
+  }
+  if (bytes > c->stage_cap) return fail(AQS_ENOMEM, "%zu bytes exceed the pinned staging", bytes);
+  *out = c->stage + c->stage_off;
+  c->stage_off += bytes;
+  return AQS_OK;
+}
+
+// The d components of an atom's values, compacted by atom id in the slot's
+// scratch, to the host.
+aqs_status read_atoms(aqs_ctx* c, int32_t rep, const double* packed, double* out) {
+  const Geom& g = c->lo.geom[rep];
+  const size_t bytes = sizeof(double) * (size_t)g.n * c->dim;
+  void* buf = nullptr;
+  aqs_status st = stage_take(c, bytes, &buf);
+  if (st) return st;
+  HIPCHK(hipMemcpyAsync(buf, packed, bytes, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  std::memcpy(out, buf, bytes);
+  c->stage_off = 0;
   return AQS_OK;
 }
 
@@ -729,6 +776,13 @@ aqs_status push_state(aqs_ctx* c) {
   HIPCHK(hipMemcpyAsync(c->d_state, c->h_state, sizeof(State) * c->n_rep, hipMemcpyHostToDevice,
                         c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  c->synced = true;
+  return AQS_OK;
+}
+
+// One slot's state to the device, behind what the stream holds.
+aqs_status push_slot(aqs_ctx* c, int32_t rep) {
+  HIPCHK(hipMemcpyAsync(c->d_state + rep, c->h_state + rep, sizeof(State), hipMemcpyHostToDevice, c->stream));
   return AQS_OK;
 }
 
@@ -739,6 +793,7 @@ Box box_of(aqs_ctx* c, int r, int64_t k) { return box_at(c->lo.geom[r], k); }
 aqs_status rebuild(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool in_loop = false,
                    int list_mode = 0) {
   if (sel.empty()) return AQS_OK;
+  c->synced = false;
   const double rl = c->rc_max + c->tn.skin;
   std::vector<int32_t> nc3(kGridInts * sel.size());
   for (size_t i = 0; i < sel.size(); ++i) {
@@ -925,8 +980,6 @@ aqs_status reset_iterations(aqs_ctx* c, Lane& L) {
   if (st) return st;
   launch_reset_iter(L.ltbl, nb, c->d_geom, c->vx, c->vy, c->vz, c->upart, c->dim, L.s);
   HIPCHK(hipGetLastError());
-  // the tables' staging is free again before the first block's start tables
-  HIPCHK(hipStreamSynchronize(L.s));
   return AQS_OK;
 }
 
@@ -965,7 +1018,7 @@ aqs_status small_launch(aqs_ctx* c, Lane& L, const IterArgs& a, int32_t start_mo
 }
 
 void free_pinned(aqs_ctx* c) {
-  std::vector<void*> ps = {c->h_state, c->h_dg};
+  std::vector<void*> ps = {c->h_state, c->h_dg, c->stage};
   for (Lane& L : c->ln) {
     for (void* p : {(void*)L.h_tbl, (void*)L.h_ftbl, (void*)L.h_tbl2, (void*)L.h_ttbl,
                     (void*)L.h_ltbl, (void*)L.h_lftbl, (void*)L.h_sel, (void*)L.h_reps,
@@ -978,6 +1031,7 @@ void free_pinned(aqs_ctx* c) {
     if (p) (void)hipHostFree(p);
   c->h_state = nullptr;
   c->h_dg = nullptr;
+  c->stage = nullptr;
 }
 
 void reset_minimizer(aqs_ctx* c, State& s);
@@ -1044,6 +1098,7 @@ bool lane_active(const aqs_ctx* c, const Lane& L) {
 // the learned-start kernels for its slots waiting in PH_LDESC); with
 // allow_timed, every prof_every-th block brackets its kernels with events.
 aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed) {
+  c->synced = false;
   const bool timed = allow_timed && c->prof_every > 0 && (c->block_count % c->prof_every) == 0;
   const int M = c->tn.block_iters;
   if (timed && !L.tiled.empty()) {
@@ -1219,21 +1274,34 @@ aqs_status finish_chains(aqs_ctx* c, const std::vector<int32_t>& sel, const int3
   if (st) return st;
   if (!records) return AQS_OK;
   const int stride = max_steps + 1;
-  std::vector<StepRecord> tmp(c->tn.log_cap);
+  // the slots' records, one wait for all of them
+  std::vector<StepRecord> pageable;
+  const size_t bytes = sizeof(StepRecord) * (size_t)n_sel * stride;
+  void* buf = nullptr;
+  if (c->stage && bytes + 64 <= c->stage_cap) {
+    st = stage_take(c, bytes, &buf);
+    if (st) return st;
+  } else {
+    pageable.resize((size_t)n_sel * stride);
+    buf = pageable.data();
+  }
+  StepRecord* tmp = static_cast<StepRecord*>(buf);
+  for (int i = 0; i < n_sel; ++i)
+    if (done[i] > 0)
+      HIPCHK(hipMemcpyAsync(tmp + (size_t)i * stride, c->log + (int64_t)sel[i] * c->tn.log_cap,
+                            sizeof(StepRecord) * std::min(done[i], stride), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  c->stage_off = 0;
   for (int i = 0; i < n_sel; ++i) {
-    const int r = sel[i];
     const int ns = done[i];
-    if (ns > 0)
-      HIPCHK(hipMemcpy(tmp.data(), c->log + (int64_t)r * c->tn.log_cap, sizeof(StepRecord) * ns,
-                       hipMemcpyDeviceToHost));
     for (int s = 0; s < ns && s < stride; ++s) {
       aqs_step_record& o = records[(int64_t)i * stride + s];
-      o.iters = tmp[s].iters;
-      o.energy = tmp[s].energy;
-      o.max_f = tmp[s].max_f;
-      o.sigma_xy = tmp[s].sigma_xy;
-      o.status = tmp[s].status;
-      o.start = tmp[s].start;
+      o.iters = tmp[(size_t)i * stride + s].iters;
+      o.energy = tmp[(size_t)i * stride + s].energy;
+      o.max_f = tmp[(size_t)i * stride + s].max_f;
+      o.sigma_xy = tmp[(size_t)i * stride + s].sigma_xy;
+      o.status = tmp[(size_t)i * stride + s].status;
+      o.start = tmp[(size_t)i * stride + s].start;
     }
     if (cancelled[i]) {
       const int last = n_steps ? n_steps[i] : 0;
@@ -1468,22 +1536,23 @@ aqs_status aqs_set_replica(aqs_ctx* c, int32_t rep, const uint8_t* types, const 
   if (rep < 0 || rep >= c->n_rep) return fail(AQS_EINVAL, "slot %d out of range", rep);
   if (!types || !pos) return fail(AQS_EINVAL, "null types or positions");
   const Geom& g = c->lo.geom[rep];
-  const int d = c->dim;
-  std::vector<double4> p(g.n);
-  std::vector<int32_t> ids(g.n);
-  for (int i = 0; i < g.n; ++i) {
+  for (int i = 0; i < g.n; ++i)
     if (types[i] > 1) return fail(AQS_EINVAL, "atom %d: type %d not in {0, 1}", i, (int)types[i]);
-    p[i] = make_double4(pos[i * d], pos[i * d + 1], d == 3 ? pos[i * d + 2] : 0.0, (double)types[i]);
-    ids[i] = i;
-  }
   aqs_status st = pull_state(c);
   if (st) return st;
-  HIPCHK(hipMemcpyAsync(c->pos4 + g.atom_off, p.data(), sizeof(double4) * g.n,
-                        hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpyAsync(c->id + g.atom_off, ids.data(), sizeof(int32_t) * g.n,
-                        hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpyAsync(c->inv + g.atom_off, ids.data(), sizeof(int32_t) * g.n,
-                        hipMemcpyHostToDevice, c->stream));
+  // the caller's arrays through pinned staging into the slot's scratch, where a
+  // kernel spreads them into the device's layout
+  const size_t xb = sizeof(double) * (size_t)g.n * c->dim, bytes = xb + (size_t)g.n;
+  void* buf = nullptr;
+  st = stage_take(c, bytes, &buf);
+  if (st) return st;
+  std::memcpy(buf, pos, xb);
+  std::memcpy((char*)buf + xb, types, (size_t)g.n);
+  char* raw = reinterpret_cast<char*>(c->tpos4 + g.atom_off);
+  HIPCHK(hipMemcpyAsync(raw, buf, bytes, hipMemcpyHostToDevice, c->stream));
+  launch_load_atoms(g, c->dim, reinterpret_cast<const double*>(raw), reinterpret_cast<const uint8_t*>(raw + xb),
+                    c->pos4, c->id, c->inv, c->stream);
+  HIPCHK(hipGetLastError());
   State& s = c->h_state[rep];
   s.k = strain_index;
   s.phase = PH_IDLE;
@@ -1491,7 +1560,7 @@ aqs_status aqs_set_replica(aqs_ctx* c, int32_t rep, const uint8_t* types, const 
   s.fmax = 0.0;
   s.status = 0;
   reset_minimizer(c, s);
-  st = push_state(c);
+  st = push_slot(c, rep);
   if (st) return st;
   c->loaded[rep] = 1;
   c->dirty[rep] = 1;
@@ -1535,21 +1604,10 @@ aqs_status aqs_get_positions(aqs_ctx* c, int32_t rep, double* pos) {
   if (st) return st;
   if (!pos) return fail(AQS_EINVAL, "null output");
   const Geom& g = c->lo.geom[rep];
-  const int d = c->dim;
-  std::vector<double4> p(g.n);
-  std::vector<int32_t> idv(g.n);
-  HIPCHK(hipMemcpyAsync(p.data(), c->pos4 + g.atom_off, sizeof(double4) * g.n,
-                        hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipMemcpyAsync(idv.data(), c->id + g.atom_off, sizeof(int32_t) * g.n,
-                        hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  for (int s = 0; s < g.n; ++s) {
-    const int i = idv[s];
-    pos[i * d] = p[s].x;
-    pos[i * d + 1] = p[s].y;
-    if (d == 3) pos[i * d + 2] = p[s].z;
-  }
-  return AQS_OK;
+  double* packed = reinterpret_cast<double*>(c->tpos4 + g.atom_off);
+  launch_pack_positions(g, c->dim, c->pos4, c->inv, packed, c->stream);
+  HIPCHK(hipGetLastError());
+  return read_atoms(c, rep, packed, pos);
 }
 
 aqs_status aqs_get_strain_index(aqs_ctx* c, int32_t rep, int64_t* k) {
@@ -1600,7 +1658,7 @@ aqs_status aqs_copy_replica(aqs_ctx* c, int32_t src, int32_t dst) {
   d.status = s.status;
   d.phase = PH_IDLE;
   reset_minimizer(c, d);
-  st = push_state(c);
+  st = push_slot(c, dst);
   if (st) return st;
   c->loaded[dst] = 1;
   c->dirty[dst] = 1;
@@ -1940,6 +1998,7 @@ aqs_status aqs_energy_forces(aqs_ctx* c, int32_t rep, double* energy, double* fo
   if (st) return st;
   st = set_table(c, L, sel, false);
   if (st) return st;
+  c->synced = false;
   IterArgs a = iter_args(c, L);
   launch_force(a, L.cur_ntiles, c->dim, c->stream);
   launch_control(a, c->stream);
@@ -1955,19 +2014,10 @@ aqs_status aqs_energy_forces(aqs_ctx* c, int32_t rep, double* energy, double* fo
   if (energy) *energy = c->h_state[rep].E;
   if (forces) {
     const Geom& g = c->lo.geom[rep];
-    const int d = c->dim;
-    std::vector<double> f[3];
-    for (int k = 0; k < d; ++k) f[k].resize(g.n);
-    std::vector<int32_t> idv(g.n);
-    double* src[3] = {c->fx, c->fy, c->fz};
-    for (int k = 0; k < d; ++k)
-      HIPCHK(hipMemcpyAsync(f[k].data(), src[k] + g.atom_off, sizeof(double) * g.n,
-                            hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(idv.data(), c->id + g.atom_off, sizeof(int32_t) * g.n,
-                          hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (int s = 0; s < g.n; ++s)
-      for (int k = 0; k < d; ++k) forces[idv[s] * d + k] = f[k][s];
+    double* packed = reinterpret_cast<double*>(c->tpos4 + g.atom_off);
+    launch_pack_columns(g, c->dim, c->fx, c->fy, c->fz, c->inv, packed, c->stream);
+    HIPCHK(hipGetLastError());
+    return read_atoms(c, rep, packed, forces);
   }
   return AQS_OK;
 }

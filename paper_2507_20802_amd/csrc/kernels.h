@@ -94,6 +94,16 @@ void launch_reset_iter(const int2* blocks, int32_t nblk, const Geom* geom, doubl
 void launch_copy_slot(const Geom* geom, int32_t src, int32_t dst, int32_t n, double4* pos4,
                       int32_t* id, int32_t* inv, hipStream_t s);
 
+// A slot's atoms from packed positions (n x dim doubles, atom-id order) and
+// types: pos4, id and inv in atom-id order (io.hip).
+void launch_load_atoms(const Geom& g, int32_t dim, const double* pos, const uint8_t* types, double4* pos4,
+                       int32_t* id, int32_t* inv, hipStream_t s);
+// ... and back: a slot's positions, or three columns, packed n x dim by atom id.
+void launch_pack_positions(const Geom& g, int32_t dim, const double4* pos4, const int32_t* inv, double* out,
+                           hipStream_t s);
+void launch_pack_columns(const Geom& g, int32_t dim, const double* x, const double* y, const double* z,
+                         const int32_t* inv, double* out, hipStream_t s);
+
 // Max minimum-image distance per block between two slots (atom-id order).
 void launch_compare(const Geom* geom, int32_t ra, int32_t rb, int32_t n, const double4* pos4,
                     const int32_t* inv, const Box& box, int32_t dim, double* part, hipStream_t s);

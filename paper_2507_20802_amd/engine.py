@@ -121,15 +121,16 @@ class Tuning:
         return t
 
 
-def _records(recs, n: int, width: int) -> np.ndarray:
-    out = np.zeros((n, width), dtype=[("iters", np.int64), ("energy", np.float64),
-                                      ("max_f", np.float64), ("sigma_xy", np.float64),
-                                      ("status", np.int32), ("start", np.int32)])
-    for i in range(n):
-        for s in range(width):
-            x = recs[i * width + s]
-            out[i, s] = (x.iters, x.energy, x.max_f, x.sigma_xy, x.status, x.start)
-    return out
+# the layout of aqs_step_record
+RECORD = np.dtype([("iters", np.int64), ("energy", np.float64), ("max_f", np.float64), ("sigma_xy", np.float64),
+                   ("status", np.int32), ("start", np.int32)])
+
+
+def _new_records(n: int) -> np.ndarray:
+    """n records for the library to fill; what it does not keeps status -1."""
+    recs = np.zeros(n, dtype=RECORD)
+    recs["status"] = -1
+    return recs
 
 
 def _i32(a) -> np.ndarray:
@@ -263,14 +264,12 @@ class Engine:
         ns = None if n_steps is None else _i32(np.broadcast_to(np.atleast_1d(n_steps), r.shape))
         sd = None if snap_dst is None else _i32(np.broadcast_to(np.atleast_1d(snap_dst), r.shape))
         width = 1 + (int(ns.max()) if ns is not None and ns.size else 0)
-        recs = (aqs_step_record * (r.size * width))()
-        for x in recs:
-            x.status = -1
+        recs = _new_records(r.size * width)
         check(self._lib.aqs_minimize_batch(self._ctx, int(r.size), _p(r, ctypes.c_int32), int(start),
                                            None if ns is None else _p(ns, ctypes.c_int32),
-                                           None if sd is None else _p(sd, ctypes.c_int32), recs),
-              "aqs_minimize_batch")
-        return _records(recs, r.size, width)
+                                           None if sd is None else _p(sd, ctypes.c_int32),
+                                           _p(recs, aqs_step_record)), "aqs_minimize_batch")
+        return recs.reshape(r.size, width)
 
     def run_round(self, chains, snaps, n_steps, start: int = AQS_START_PLAIN, delta_eq: float = 1e-4,
                   live: bool = False, abandon: bool = False):
@@ -288,15 +287,14 @@ class Engine:
         sn = _i32(np.broadcast_to(np.atleast_1d(snaps), c.shape))
         ns = _i32(np.broadcast_to(np.atleast_1d(n_steps), c.shape))
         width = 1 + int(ns.max())
-        recs = (aqs_step_record * (P * width))()
-        for x in recs:
-            x.status = -1
+        recs = _new_records(P * width)
         chk = (aqs_check * P)()
         check(self._lib.aqs_run_round(self._ctx, P, _p(c, ctypes.c_int32), _p(sn, ctypes.c_int32),
                                       _p(ns, ctypes.c_int32), int(start), float(delta_eq),
-                                      (2 if abandon else 1) if live else 0, recs, chk), "aqs_run_round")
+                                      (2 if abandon else 1) if live else 0, _p(recs, aqs_step_record), chk),
+              "aqs_run_round")
         checks = [(int(x.decided), bool(x.equal), x.max_disp, x.de_per_atom) for x in chk]
-        return _records(recs, P, width), checks
+        return recs.reshape(P, width), checks
 
     def compare(self, a: int, b: int, delta_eq: float = 1e-4):
         """(equal, max_disp, dE/N) of the equality test, Eq. (20)."""
