@@ -3,20 +3,20 @@
 //
 // Steps (one launch each, all on the context stream):
 //   grid   copy the host-chosen cell grid into the slot state
-//   zero   clear per-cell counts
 //   bin    fractional coordinates s = H^-1 r (Eq. 1 box); wrap r into the
-//          primary cell (r -= H floor(s)); cell index; integer atomic count
-//   scan   exclusive scan of the counts per slot (one workgroup per slot)
-//   scat   place each atom in its cell (order inside a cell arbitrary)
-//   sort   sort each cell by atom id (gives a deterministic order)
-//   perm   gather positions, velocities, ids into scratch in the new order
-//   back   copy back; inverse permutation
+//          primary cell (r -= H floor(s)); cell index; place in the cell from
+//          an integer atomic count
+//   scan   exclusive scan of the counts per slot (one workgroup per slot); the
+//          counts are cleared for the next rebuild
+//   scat   each atom to its place (order inside a cell arbitrary)
+//   perm   per cell: its atoms by id (gives a deterministic order), their
+//          positions, velocities, ids into scratch
+//   back   copy back; inverse permutation; the slot's build state
 //   list   per force tile (tiles.h): its segment and halo run table, then
 //          per cell of it the atoms against the 3^dim neighbouring cells,
 //          keeping every image pair within rc_ab + skin; tiles with an LDS halo get the packed list
 //          (16-bit byte offsets 8 h of the neighbour's halo slot h), the
 //          others the word list (j | image code << 24); engine.h
-//   done   reset the validity bound of each rebuilt slot
 // Integer atomics only; the result does not depend on their order.
 #include <hip/hip_runtime.h>
 
@@ -43,16 +43,6 @@ __global__ void k_rb_grid(RebuildArgs a, const int32_t* nc3) {
   }
 }
 
-__global__ void k_rb_zero(RebuildArgs a) {
-  const int rep = a.reps[blockIdx.y];
-  const Geom& g = a.geom[rep];
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c <= g.cell_cap) {
-    a.cell_count[g.cell_off + c] = 0;
-    a.cell_start[g.cell_off + c] = 0;
-  }
-}
-
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_rb_bin(RebuildArgs a) {
   const int2 bt = a.blocks[blockIdx.x];
@@ -60,14 +50,14 @@ __global__ __launch_bounds__(kBlock) void k_rb_bin(RebuildArgs a) {
   const Geom g = a.geom[bt.x];
   const State* st = a.state + bt.x;
   const int li = bt.y * kBlock + threadIdx.x;
-  if (li >= g.n) return;
-  const int64_t gi = g.atom_off + li;
+  const bool live = li < g.n;
+  const int64_t gi = g.atom_off + min(li, g.n - 1);
   const Box b = box_at(g, st->k);
   double4 p = a.pos4[gi];
   double s[3];
   frac(b, p.x, p.y, (D == 3) ? p.z : 0.0, s);
   const double nx = floor(s[0]), ny = floor(s[1]), nz = (D == 3) ? floor(s[2]) : 0.0;
-  if (nx != 0.0 || ny != 0.0 || nz != 0.0) {
+  if (live && (nx != 0.0 || ny != 0.0 || nz != 0.0)) {
     // back into the box: r -= H n
     p.x -= nx * b.h00 + ny * b.h01;
     p.y -= (b.h10 == 0.0) ? ny * b.h11 : nx * b.h10 + ny * b.h11;
@@ -84,8 +74,25 @@ __global__ __launch_bounds__(kBlock) void k_rb_bin(RebuildArgs a) {
   int c3[3];
   const int nc[3] = {st->nc[0], st->nc[1], st->nc[2]};
   const int c = cell_of_pos<D>(b, nc, p, c3);
+  // Its place among the cell's atoms, which the scatter uses (a second pass of
+  // atomics there took 17 us for one replica of 32768 atoms, 64 for 16).  Atoms
+  // in memory order mostly share their neighbour's cell: one atomic per run of
+  // lanes in the same cell.
+  const int lane = threadIdx.x % kWave;
+  const int key = live ? c : -1;
+  const int before = __shfl_up(key, 1, kWave);
+  const bool head = lane == 0 || key != before;
+  const unsigned long long heads = __ballot(head);
+  const int start = kWave - 1 - __clzll((long long)(heads & (~0ull >> (kWave - 1 - lane))));
+  const unsigned long long later = lane == kWave - 1 ? 0ull : heads & (~0ull << (lane + 1));
+  int base = 0;
+  if (live && head)
+    base = atomicAdd(a.cell_count + g.cell_off + c,
+                     (later ? __ffsll((long long)later) - 1 : kWave) - lane);
+  base = __shfl(base, start, kWave);
+  if (!live) return;
   a.cell_of[gi] = c;
-  atomicAdd(a.cell_count + g.cell_off + c, 1);
+  a.tid_[gi] = base + lane - start;
 }
 
 __global__ __launch_bounds__(1024) void k_rb_scan(RebuildArgs a) {
@@ -112,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_rb_scan(RebuildArgs a) {
   for (int c = c0; c < c1; ++c) {
     const int n = a.cell_count[g.cell_off + c];
     a.cell_start[g.cell_off + c] = run;
-    a.cell_count[g.cell_off + c] = run;  // becomes the scatter cursor
+    a.cell_count[g.cell_off + c] = 0;   // for the next rebuild
     run += n;
   }
   if (threadIdx.x == T - 1) a.cell_start[g.cell_off + ncell] = part[T - 1];
@@ -126,18 +133,18 @@ __global__ __launch_bounds__(kBlock) void k_rb_scatter(RebuildArgs a) {
   if (li >= g.n) return;
   const int64_t gi = g.atom_off + li;
   const int c = a.cell_of[gi];
-  const int pos = atomicAdd(a.cell_count + g.cell_off + c, 1);
-  a.order[g.atom_off + pos] = li;
+  a.order[g.atom_off + a.cell_start[g.cell_off + c] + a.tid_[gi]] = li;
 }
 
-// Sort each cell by atom id: one wavefront per cell (4 cells per block).
-// Each atom's new place is its rank among the cell's ids (ids are distinct),
-// counted against a copy of the cell in LDS.  Cells larger than kSortCap
-// (only possible for very dense random starts) fall back to an insertion
-// sort by one lane.
+// Atoms of a cell by id, moved to their new places: one wavefront per cell (4
+// cells per block).  An atom's new place is its rank among the cell's ids
+// (ids are distinct), counted against a copy of the cell in LDS.  Cells larger
+// than kSortCap (only possible for very dense random starts) are sorted in
+// memory by one lane.
 constexpr int kSortCap = 192;
 
-__global__ __launch_bounds__(256) void k_rb_sort(RebuildArgs a) {
+template <int D>
+__global__ __launch_bounds__(256) void k_rb_perm(RebuildArgs a) {
   const int rep = a.reps[blockIdx.y];
   const Geom g = a.geom[rep];
   const State* st = a.state + rep;
@@ -145,7 +152,6 @@ __global__ __launch_bounds__(256) void k_rb_sort(RebuildArgs a) {
   const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int c = blockIdx.x * 4 + wv;
   __shared__ int keys[4][kSortCap];
-  __shared__ int vals[4][kSortCap];
   int b = 0, n = 0;
   int32_t* o = a.order + g.atom_off;
   const int32_t* id = a.id + g.atom_off;
@@ -154,20 +160,8 @@ __global__ __launch_bounds__(256) void k_rb_sort(RebuildArgs a) {
     n = a.cell_start[g.cell_off + c + 1] - b;
   }
   const bool fits = n <= kSortCap;
-  if (fits)
-    for (int k = lane; k < n; k += kWave) {
-      const int v = o[b + k];
-      vals[wv][k] = v;
-      keys[wv][k] = id[v];
-    }
-  __syncthreads();
   if (fits) {
-    for (int k = lane; k < n; k += kWave) {
-      const int key = keys[wv][k];
-      int r = 0;
-      for (int q = 0; q < n; ++q) r += (keys[wv][q] < key) ? 1 : 0;
-      o[b + r] = vals[wv][k];
-    }
+    for (int k = lane; k < n; k += kWave) keys[wv][k] = id[o[b + k]];
   } else if (lane == 0) {
     for (int i = b + 1; i < b + n; ++i) {  // insertion sort by atom id
       const int v = o[i];
@@ -180,28 +174,28 @@ __global__ __launch_bounds__(256) void k_rb_sort(RebuildArgs a) {
       o[j + 1] = v;
     }
   }
-}
-
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_rb_perm(RebuildArgs a) {
-  const int2 bt = a.blocks[blockIdx.x];
-  if (bt.x < 0) return;
-  const Geom g = a.geom[bt.x];
-  const int li = bt.y * kBlock + threadIdx.x;
-  if (li >= g.n) return;
-  const int64_t gi = g.atom_off + li;
-  const int64_t go = g.atom_off + a.order[gi];
-  a.tpos4[gi] = a.pos4[go];
-  a.tvx[gi] = a.vx[go];
-  a.tvy[gi] = a.vy[go];
-  if (D == 3) a.tvz[gi] = a.vz[go];
-  a.tid_[gi] = a.id[go];
-  if (a.dlx) {
-    a.tdlx[gi] = a.dlx[go];
-    a.tdly[gi] = a.dly[go];
-    if (D == 3) a.tdlz[gi] = a.dlz[go];
+  __syncthreads();
+  for (int k = lane; k < n; k += kWave) {
+    const int v = o[b + k];
+    int r = k;
+    if (fits) {
+      const int key = keys[wv][k];
+      r = 0;
+      for (int q = 0; q < n; ++q) r += (keys[wv][q] < key) ? 1 : 0;
+    }
+    const int64_t go = g.atom_off + v, gi = g.atom_off + b + r;
+    a.tpos4[gi] = a.pos4[go];
+    a.tvx[gi] = a.vx[go];
+    a.tvy[gi] = a.vy[go];
+    if (D == 3) a.tvz[gi] = a.vz[go];
+    a.tid_[gi] = a.id[go];
+    if (a.dlx) {
+      a.tdlx[gi] = a.dlx[go];
+      a.tdly[gi] = a.dly[go];
+      if (D == 3) a.tdlz[gi] = a.dlz[go];
+    }
+    if (a.alt4) a.talt4[gi] = a.alt4[go];
   }
-  if (a.alt4) a.talt4[gi] = a.alt4[go];
 }
 
 template <int D>
@@ -210,6 +204,20 @@ __global__ __launch_bounds__(kBlock) void k_rb_back(RebuildArgs a) {
   if (bt.x < 0) return;
   const Geom g = a.geom[bt.x];
   const int li = bt.y * kBlock + threadIdx.x;
+  if (threadIdx.x == 0) {
+    a.upart[g.block0 + bt.y] = 0.0;   // no displacement since this build
+    if (bt.y == 0) {
+      State* st = a.state + bt.x;
+      st->ubound = 0.0;
+      st->gamma_build = strain_of(st->k, g.dgamma);
+      st->k_build = st->k;
+      if (a.resume && st->phase == PH_REBUILD)
+        st->phase = (st->resume_phase == PH_LPLAIN || st->resume_phase == PH_LMOVE ||
+                     st->resume_phase == PH_LREVERT || st->resume_phase == PH_CG)
+                        ? st->resume_phase
+                        : PH_FIRE;
+    }
+  }
   if (li >= g.n) return;
   const int64_t gi = g.atom_off + li;
   a.pos4[gi] = a.tpos4[gi];
@@ -732,31 +740,12 @@ __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4)))
   }
 }
 
-__global__ void k_rb_done(RebuildArgs a) {
-  const int rep = a.reps[blockIdx.x];
-  const Geom& g = a.geom[rep];
-  State* st = a.state + rep;
-  for (int b = threadIdx.x; b < g.nblocks; b += blockDim.x) a.upart[g.block0 + b] = 0.0;
-  if (threadIdx.x == 0) {
-    st->ubound = 0.0;
-    st->gamma_build = strain_of(st->k, g.dgamma);
-    st->k_build = st->k;
-    if (a.resume && st->phase == PH_REBUILD)
-      st->phase = (st->resume_phase == PH_LPLAIN || st->resume_phase == PH_LMOVE ||
-                   st->resume_phase == PH_LREVERT || st->resume_phase == PH_CG)
-                      ? st->resume_phase
-                      : PH_FIRE;
-  }
-}
-
 }  // namespace
 
 void launch_rebuild(const RebuildArgs& a, int32_t max_cells_per_slot, hipStream_t s,
                     const int32_t* nc3_dev) {
   if (a.nreps <= 0 || a.nblk <= 0) return;
-  const int cb = (max_cells_per_slot + 1 + 255) / 256;
   hipLaunchKernelGGL(k_rb_grid, dim3(a.nreps), dim3(64), 0, s, a, nc3_dev);
-  hipLaunchKernelGGL(k_rb_zero, dim3(cb, a.nreps), dim3(256), 0, s, a);
   if (a.dim == 3) {
     hipLaunchKernelGGL(k_rb_bin<3>, dim3(a.nblk), dim3(kBlock), 0, s, a);
   } else {
@@ -764,17 +753,16 @@ void launch_rebuild(const RebuildArgs& a, int32_t max_cells_per_slot, hipStream_
   }
   hipLaunchKernelGGL(k_rb_scan, dim3(a.nreps), dim3(1024), 0, s, a);
   hipLaunchKernelGGL(k_rb_scatter, dim3(a.nblk), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_rb_sort, dim3((max_cells_per_slot + 3) / 4, a.nreps), dim3(256), 0, s, a);
+  const dim3 per_cell((max_cells_per_slot + 3) / 4, a.nreps);
   if (a.dim == 3) {
-    hipLaunchKernelGGL(k_rb_perm<3>, dim3(a.nblk), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_rb_perm<3>, per_cell, dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_rb_back<3>, dim3(a.nblk), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_rb_list<3>, dim3(a.ntile_blk), dim3(kListBlock), 0, s, a);
   } else {
-    hipLaunchKernelGGL(k_rb_perm<2>, dim3(a.nblk), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_rb_perm<2>, per_cell, dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_rb_back<2>, dim3(a.nblk), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_rb_list<2>, dim3(a.ntile_blk), dim3(kListBlock), 0, s, a);
   }
-  hipLaunchKernelGGL(k_rb_done, dim3(a.nreps), dim3(256), 0, s, a);
 }
 
 }  // namespace aqs
