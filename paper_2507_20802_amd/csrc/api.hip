@@ -241,7 +241,9 @@ aqs_status make_layout(const aqs_potential* pot, const Tune& tn, int n_rep, cons
     lo.o_small[l] = take(sizeof(int32_t) * n_rep);
   }
   lo.o_dg = take(sizeof(double) * 4 * n_rep);
-  lo.o_red = take(sizeof(double) * 10 * ((size_t)lo.blocks + 8));
+  int32_t most_tiles = 0;
+  for (const Geom& g : lo.geom) most_tiles = std::max(most_tiles, g.tile_cap);
+  lo.o_red = take(sizeof(double) * 10 * ((size_t)std::max(lo.blocks, most_tiles) + 8));
   for (int a = 0; a < 3; ++a) lo.o_dl[a] = take(sizeof(double) * A);
   for (int a = 0; a < 3; ++a) lo.o_tdl[a] = take(sizeof(double) * A);
   lo.o_alt4 = take(sizeof(double4) * A);
@@ -1959,19 +1961,23 @@ aqs_status aqs_stress(aqs_ctx* c, int32_t rep, double* sigma, double* energy) {
   st = pull_state(c);
   if (st) return st;
   std::vector<int32_t> sel(1, rep);
-  st = rebuild(c, c->ln[0], sel, false, 1);  // global-index entries for the virial kernel
+  // the force kernel's lists; an atom whose neighbours do not fill whole groups
+  // within the capacity may still fit in a word list
+  st = rebuild(c, c->ln[0], sel, false);
+  if (st == AQS_ECAPACITY) st = rebuild(c, c->ln[0], sel, false, 1);
   if (st) return st;
   const Geom& g = c->lo.geom[rep];
   IterArgs a = iter_args(c, c->ln[0]);
   const Box bx = box_of(c, rep, c->h_state[rep].k);
-  launch_virial(a, rep, g.nblocks, c->dim, bx, c->red, c->stream);
+  const int ntiles = c->tiles_now[rep];
+  launch_virial(a, rep, ntiles, c->dim, bx, c->red, c->stream);
   HIPCHK(hipGetLastError());
-  std::vector<double> part((size_t)g.nblocks * 10);
+  std::vector<double> part((size_t)ntiles * 10);
   HIPCHK(hipMemcpyAsync(part.data(), c->red, sizeof(double) * part.size(), hipMemcpyDeviceToHost,
                         c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   double tot[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int b = 0; b < g.nblocks; ++b)
+  for (int b = 0; b < ntiles; ++b)
     for (int k = 0; k < 10; ++k) tot[k] += part[(size_t)b * 10 + k];
   // simple shear keeps V = Lx Ly Lz; the pure shear of Eq. (17) scales the (x, y) area
   const double vol = (bx.h10 == 0.0) ? g.L[0] * g.L[1] * g.L[2]

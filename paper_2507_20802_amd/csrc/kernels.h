@@ -108,8 +108,8 @@ void launch_pack_columns(const Geom& g, int32_t dim, const double* x, const doub
 void launch_compare(const Geom* geom, int32_t ra, int32_t rb, int32_t n, const double4* pos4,
                     const int32_t* inv, const Box& box, int32_t dim, double* part, hipStream_t s);
 
-// Energy and full virial per block of one slot: 1 + 9 doubles per block.
-void launch_virial(const IterArgs& a, int32_t rep, int32_t nblocks, int32_t dim, const Box& box,
+// Energy and full virial per force tile of one slot: 1 + 9 doubles per tile.
+void launch_virial(const IterArgs& a, int32_t rep, int32_t ntiles, int32_t dim, const Box& box,
                    double* part, hipStream_t s);
 
 }  // namespace aqs
