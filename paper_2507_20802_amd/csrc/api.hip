@@ -294,6 +294,11 @@ struct Lane {
   int32_t g_iters = 0;
   int32_t g_pad = 0;               // its force launches' dynamic LDS
   bool in_flight = false;          // a block of iterations launched, not yet polled
+  int32_t launched = 0;            // ... and its iterations
+  // block length (block_length): iterations since the tiled slots last all
+  // waited for the host, and those between such waits, the last two times
+  int32_t span = 0, waits[2] = {0, 0};
+  std::vector<uint32_t> ran0;      // the tiled slots' State.ran at the block's start
   bool timed = false;              // ... with HIP events around its kernels
   bool prefetched = false;         // ... with its slots' states copied back behind it
   uint32_t xcd_mask = kAllXcds;    // XCDs its launch tables place blocks on
@@ -980,6 +985,7 @@ aqs_status reset_iterations(aqs_ctx* c, Lane& L) {
   int32_t nb = 0, nt = 0;
   aqs_status st = start_tables(c, L, L.cur_sel, &nb, &nt);
   if (st) return st;
+  L.span = L.waits[0] = L.waits[1] = 0;
   launch_reset_iter(L.ltbl, nb, c->d_geom, c->vx, c->vy, c->vz, c->upart, c->dim, L.s);
   HIPCHK(hipGetLastError());
   return AQS_OK;
@@ -1096,13 +1102,57 @@ bool lane_active(const aqs_ctx* c, const Lane& L) {
   return false;
 }
 
-// One block of block_iters FIRE iterations over the lane's selection (after
+// Iterations of the lane's next block.  A slot that waits for the host (a list
+// rebuild, a predicted start) sits out the rest of its block in launches that
+// only read its phase, 6 us an iteration; ending a block costs a read-back and
+// the launches' start, about 20 us.  While all slots wait together, a block is
+// therefore as long as the iterations between such waits have lately been
+// (the longer of the last two, plus an eighth); past that length the iterations
+// so far are doubled.  32768 atoms that need new lists every 10 iterations:
+// 20 steps took 16.4 ms, now 14.6; 16 replicas of them 52, now 44.  block_iters is
+// the longest block; all blocks have that length where some slots run on while
+// others wait (ending those early would rebuild fewer slots at a time), where
+// they are captured, and in a live round.
+constexpr int kMinBlock = 4;
+int block_length(const aqs_ctx* c, const Lane& L) {
+  const int most = c->tn.block_iters;
+  const int wait = std::max(L.waits[0], L.waits[1]);
+  if (wait <= 0 || c->tn.use_graph || c->live) return most;
+  const int n = L.span > 0 ? L.span : wait + wait / 8 + 2;
+  return std::min(most, std::max(kMinBlock, (n + 1) / 2 * 2));
+}
+
+// After a block: what its tiled slots ran.
+void note_block(const aqs_ctx* c, Lane& L) {
+  int ran = 0;
+  bool some = false, all = true;
+  for (size_t i = 0; i < L.tiled.size(); ++i) {
+    const State& s = c->h_state[L.tiled[i]];
+    if (s.phase == PH_DONE) continue;
+    some = true;
+    all = all && (s.phase == PH_REBUILD || s.phase == PH_LDESC);
+    ran = std::max(ran, (int)(s.ran - L.ran0[i]));
+  }
+  if (!some) return;
+  if (!all) {
+    L.span = std::min(L.span + L.launched, 1 << 20);
+    return;
+  }
+  L.waits[1] = L.waits[0];
+  L.waits[0] = std::max(1, L.span + ran);
+  L.span = 0;
+}
+
+// One block of FIRE iterations (block_length) over the lane's selection (after
 // the learned-start kernels for its slots waiting in PH_LDESC); with
 // allow_timed, every prof_every-th block brackets its kernels with events.
 aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed) {
   c->synced = false;
   const bool timed = allow_timed && c->prof_every > 0 && (c->block_count % c->prof_every) == 0;
-  const int M = c->tn.block_iters;
+  const int M = block_length(c, L);
+  L.launched = M;
+  L.ran0.clear();
+  for (int r : L.tiled) L.ran0.push_back(c->h_state[r].ran);
   if (timed && !L.tiled.empty()) {
     while ((int)L.ev.size() < 4 * M) {
       hipEvent_t e;
@@ -1184,7 +1234,7 @@ aqs_status lane_poll(aqs_ctx* c, Lane& L, bool all_states, int& active) {
   ++c->cnt.host_polls;
   L.in_flight = false;
   if (L.timed) {
-    const int M = c->tn.block_iters;
+    const int M = L.launched;
     for (int it = 0; it < M; ++it) {
       float f = 0.f, u = 0.f;
       HIPCHK(hipEventElapsedTime(&f, L.ev[4 * it + 0], L.ev[4 * it + 1]));
@@ -1203,6 +1253,7 @@ aqs_status lane_poll(aqs_ctx* c, Lane& L, bool all_states, int& active) {
     ++c->cnt.force_timed;
     L.small_timed = false;
   }
+  note_block(c, L);
   std::vector<int32_t> rb;
   active = 0;
   for (int r : L.cur_sel) {

@@ -168,6 +168,7 @@ struct State {
   int32_t list_mode;  // 0: tiles index their LDS halo; 1: global indices only
   int32_t resume_phase;  // phase to resume after a neighbour-list rebuild
   int32_t drops;      // fine steps of this call whose shear stress fell below the step before's
+  uint32_t ran;       // iterations computed by the tiles' launches (modulo 2^32)
   double sxy_prev;    // shear stress of the last finished minimisation
   int64_t k_build;    // strain index at the last neighbour-list build
 };

@@ -386,6 +386,7 @@ __device__ __forceinline__ void copy_state(State& d, const State& s) {
   d.list_mode = s.list_mode;
   d.resume_phase = s.resume_phase;
   d.drops = s.drops;
+  d.ran = s.ran;
   d.sxy_prev = s.sxy_prev;
   d.k_build = s.k_build;
 }
@@ -1124,6 +1125,7 @@ __global__ __launch_bounds__(kBlock) void k_step(IterArgs a) {
         atomicAdd(a.evals, (unsigned long long)g.n);
         if (a.tevals) atomicAdd(a.tevals, (unsigned long long)g.n);
       }
+      if (compute) ss.ran += 1u;
       control<CG>(a, rep, g, r, phase0, ss, sq, owner);
     }
     __syncthreads();
