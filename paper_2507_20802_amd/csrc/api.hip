@@ -356,7 +356,8 @@ struct aqs_ctx {
   // host mirrors
   State* h_state = nullptr;  // pinned
   // h_state holds what the device does: set by a whole read-back or write, off
-  // once a kernel that writes states is launched
+  // once a kernel that writes states is launched (from lane_launch on until the
+  // block has been read back, whatever its starts read meanwhile)
   bool synced = false;
   // pinned staging of atoms, a ring without wrap: what is taken stays in use
   // until the context stream has been waited for
@@ -800,6 +801,7 @@ Box box_of(aqs_ctx* c, int r, int64_t k) { return box_at(c->lo.geom[r], k); }
 aqs_status rebuild(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool in_loop = false,
                    int list_mode = 0) {
   if (sel.empty()) return AQS_OK;
+  const bool whole = c->synced;   // nothing else is running
   c->synced = false;
   const double rl = c->rc_max + c->tn.skin;
   std::vector<int32_t> nc3(kGridInts * sel.size());
@@ -869,9 +871,11 @@ aqs_status rebuild(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool in
   ++c->cnt.rebuilds;
   for (int r : sel) c->dirty[r] = 0;
   // in the minimisation loop the next poll reads the overflow flag and the
-  // state; elsewhere check now
+  // state; elsewhere check now.  Within a lane's launch (a linear start's lists)
+  // only its own slots are read, on its stream: the mirror stays open, so the
+  // poll behind the block waits for it
   if (in_loop) return AQS_OK;
-  aqs_status st = pull_state(c);
+  aqs_status st = whole ? pull_state(c) : pull_slots(c, L, sel);
   if (st) return st;
   return check_overflow(c, L);
 }
