@@ -54,7 +54,7 @@ double rc_max_of(const aqs_potential* p) {
 // kXcds (engine.h).
 constexpr uint32_t kAllXcds = (1u << kXcds) - 1u;
 
-// pinned staging kept for many small slots (one slot always fits)
+// pinned staging for the records of many small slots (one slot's atoms always fit)
 constexpr size_t kStageBytes = size_t(4) << 20;
 // blocks of iterations in one launch of k_small that nothing waits for
 constexpr int kSmallBlocks = 16;
@@ -359,10 +359,10 @@ struct aqs_ctx {
   // once a kernel that writes states is launched (from lane_launch on until the
   // block has been read back, whatever its starts read meanwhile)
   bool synced = false;
-  // pinned staging of atoms, a ring without wrap: what is taken stays in use
-  // until the context stream has been waited for
+  // pinned staging of atoms and records: each call that uses it waits for the
+  // context stream before it returns
   char* stage = nullptr;
-  size_t stage_cap = 0, stage_off = 0;
+  size_t stage_cap = 0;
   std::vector<char> loaded, dirty;
   std::vector<int32_t> tiles_now;  // force tiles of each slot's current grid
   // driver lanes (pinned staging: one use per synchronisation of the lane)
@@ -708,28 +708,20 @@ aqs_status pull_state(aqs_ctx* c) {
                         L.s));
   HIPCHK(hipMemcpyAsync(L.h_over, L.overflow, sizeof(int32_t), hipMemcpyDeviceToHost, L.s));
   HIPCHK(hipStreamSynchronize(L.s));
-  c->stage_off = 0;
   c->synced = true;
   return AQS_OK;
 }
 
-// bytes of pinned staging, free until the context stream is next waited for
+// bytes of pinned staging, the caller's until it returns
 aqs_status stage_take(aqs_ctx* c, size_t bytes, void** out) {
-  bytes = align_up(bytes, 64);
   if (!c->stage) {
     size_t most = 0;
-    for (const Geom& g : c->lo.geom) most = std::max(most, (size_t)g.n * (8 * c->dim + 1) + 64);
-    c->stage_cap = align_up(std::max(most, std::min(kStageBytes, most * c->n_rep)), 64);
+    for (const Geom& g : c->lo.geom) most = std::max(most, (size_t)g.n * (8 * c->dim + 1));
+    c->stage_cap = std::max(most, std::min(kStageBytes, most * c->n_rep));
     HIPCHK(hipHostMalloc((void**)&c->stage, c->stage_cap, hipHostMallocDefault));
-    c->stage_off = 0;
-  }
-  if (c->stage_off + bytes > c->stage_cap) {
-    HIPCHK(hipStreamSynchronize(c->stream));
-    c->stage_off = 0;
   }
   if (bytes > c->stage_cap) return fail(AQS_ENOMEM, "%zu bytes exceed the pinned staging", bytes);
-  *out = c->stage + c->stage_off;
-  c->stage_off += bytes;
+  *out = c->stage;
   return AQS_OK;
 }
 
@@ -744,7 +736,6 @@ aqs_status read_atoms(aqs_ctx* c, int32_t rep, const double* packed, double* out
   HIPCHK(hipMemcpyAsync(buf, packed, bytes, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   std::memcpy(out, buf, bytes);
-  c->stage_off = 0;
   return AQS_OK;
 }
 
@@ -788,9 +779,11 @@ aqs_status push_state(aqs_ctx* c) {
   return AQS_OK;
 }
 
-// One slot's state to the device, behind what the stream holds.
+// One slot's state to the device, and the end of what the stream holds waited
+// for: the slot's atoms are loaded, and what went wrong is this call's error.
 aqs_status push_slot(aqs_ctx* c, int32_t rep) {
   HIPCHK(hipMemcpyAsync(c->d_state + rep, c->h_state + rep, sizeof(State), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
   return AQS_OK;
 }
 
@@ -1335,7 +1328,7 @@ aqs_status finish_chains(aqs_ctx* c, const std::vector<int32_t>& sel, const int3
   std::vector<StepRecord> pageable;
   const size_t bytes = sizeof(StepRecord) * (size_t)n_sel * stride;
   void* buf = nullptr;
-  if (c->stage && bytes + 64 <= c->stage_cap) {
+  if (c->stage && bytes <= c->stage_cap) {
     st = stage_take(c, bytes, &buf);
     if (st) return st;
   } else {
@@ -1348,7 +1341,6 @@ aqs_status finish_chains(aqs_ctx* c, const std::vector<int32_t>& sel, const int3
       HIPCHK(hipMemcpyAsync(tmp + (size_t)i * stride, c->log + (int64_t)sel[i] * c->tn.log_cap,
                             sizeof(StepRecord) * std::min(done[i], stride), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
-  c->stage_off = 0;
   for (int i = 0; i < n_sel; ++i) {
     const int ns = done[i];
     for (int s = 0; s < ns && s < stride; ++s) {

@@ -403,12 +403,28 @@ void linear_start_polls(bool profiled) {
   call(aqs_destroy(k.c), "destroy");
 }
 
+// Loading and copying a slot are over when the calls return.
+void slot_loads_wait() {
+  Case k({100, 100});
+  for (int r = 0; r < 2; ++r) {
+    call(k.load(r), "set_replica");
+    expect(of(k.stream)->idle(), "aqs_set_replica returned with work in its stream");
+  }
+  call(aqs_copy_replica(k.c, 0, 1), "copy_replica");
+  expect(of(k.stream)->idle(), "aqs_copy_replica returned with work in its stream");
+  std::vector<double> x(200);
+  call(aqs_get_positions(k.c, 0, x.data()), "get_positions");
+  expect(x == k.pos[0], "the positions as they were loaded");
+  call(aqs_destroy(k.c), "destroy");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "linear_start_polls") linear_start_polls(false);
   else if (what == "linear_start_polls_profiled") linear_start_polls(true);
+  else if (what == "slot_loads_wait") slot_loads_wait();
   else wrong("no such scenario");
   std::printf("ok\n");
   return 0;
