@@ -285,6 +285,7 @@ struct Lane {
   int32_t nsmall = 0, nhalf = 0;   // ... and the number that k_small runs (small_d; nhalf: up to kSmallHalf atoms)
   hipStream_t side = nullptr;      // k_small beside the tiles' launches
   hipEvent_t fork = nullptr, join = nullptr;
+  bool beside = false;             // ... and it has work there that the lane's stream does not wait for yet
   hipEvent_t small_ev[2] = {nullptr, nullptr};   // its timing events
   bool small_timed = false;
   int32_t cur_nblk = 0;
@@ -988,19 +989,34 @@ aqs_status reset_iterations(aqs_ctx* c, Lane& L) {
   return AQS_OK;
 }
 
+// What follows on the lane's stream waits for its side stream.
+hipError_t join_side(Lane& L) {
+  if (!L.beside) return hipSuccess;
+  L.beside = false;
+  hipError_t e = hipEventRecord(L.join, L.side);
+  if (e == hipSuccess) e = hipStreamWaitEvent(L.s, L.join, 0);
+  if (e != hipSuccess) (void)hipStreamSynchronize(L.side);
+  return e;
+}
+
+// ... also where a launch ends early with an error
+struct SideJoined {
+  Lane& L;
+  ~SideJoined() { (void)join_side(L); }
+};
+
 // k_small over the lane's small slots, `iters` iterations at most, on the lane's
 // stream; beside the tiles' launches when there are any, on a stream of its
-// own, so that neither waits for the other within a block.
+// own, so that neither waits for the other within a block (the caller joins it).
 aqs_status small_launch(aqs_ctx* c, Lane& L, const IterArgs& a, int32_t start_mode, int iters) {
   hipStream_t s = L.s;
   if (!L.tiled.empty()) {
-    if (!L.side) {
-      HIPCHK(hipStreamCreateWithFlags(&L.side, hipStreamNonBlocking));
-      HIPCHK(hipEventCreateWithFlags(&L.fork, hipEventDisableTiming));
-      HIPCHK(hipEventCreateWithFlags(&L.join, hipEventDisableTiming));
-    }
+    if (!L.side) HIPCHK(hipStreamCreateWithFlags(&L.side, hipStreamNonBlocking));
+    for (hipEvent_t* e : {&L.fork, &L.join})
+      if (!*e) HIPCHK(hipEventCreateWithFlags(e, hipEventDisableTiming));
     HIPCHK(hipEventRecord(L.fork, L.s));
     HIPCHK(hipStreamWaitEvent(L.side, L.fork, 0));
+    L.beside = true;
     s = L.side;
   }
   SmallArgs sa{};
@@ -1017,7 +1033,6 @@ aqs_status small_launch(aqs_ctx* c, Lane& L, const IterArgs& a, int32_t start_mo
       if (!e) HIPCHK(hipEventCreate(&e));
   HIPCHK(launch_small(sa, L.nhalf, L.nsmall - L.nhalf, s, a.tevals ? L.small_ev[0] : nullptr, a.tevals ? L.small_ev[1] : nullptr));
   L.small_timed = a.tevals != nullptr;
-  if (s != L.s) HIPCHK(hipEventRecord(L.join, s));
   ++c->cnt.force_launches;
   return AQS_OK;
 }
@@ -1173,6 +1188,7 @@ aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed
   IterArgs a = iter_args(c, L);
   if (timed) a.tevals = c->evals + 1;   // atoms of the timed launches
   L.small_timed = false;
+  SideJoined joined{L};
   if (L.nsmall > 0) {
     // Alone, a plain or extrapolated chain needs the host only at its end, so
     // a launch holds many blocks (a slot that ends leaves it early, the launch
@@ -1197,10 +1213,8 @@ aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed
     if (st) return st;
   }
   HIPCHK(hipGetLastError());
-  if (!L.tiled.empty()) {
-    c->cnt.force_launches += M;
-    if (L.nsmall > 0) HIPCHK(hipStreamWaitEvent(L.s, L.join, 0));
-  }
+  HIPCHK(join_side(L));
+  if (!L.tiled.empty()) c->cnt.force_launches += M;
   if (allow_timed) ++c->block_count;
   L.prefetched = false;
   if (c->live) {
@@ -1562,6 +1576,8 @@ aqs_status aqs_create(const aqs_potential* pot, const aqs_fire_params* fire,
 
 aqs_status aqs_destroy(aqs_ctx* c) {
   if (!c) return AQS_OK;
+  for (Lane& L : c->ln)
+    if (L.side) (void)hipStreamSynchronize(L.side);
   (void)hipStreamSynchronize(c->stream);
   if (c->ln[1].s) {
     (void)hipStreamSynchronize(c->ln[1].s);

@@ -418,6 +418,25 @@ void slot_loads_wait() {
   call(aqs_destroy(k.c), "destroy");
 }
 
+// A launch that fails beside work on the side stream: the lane's stream still
+// waits for that work, and so does the context's end.
+void side_stream_joins(bool destroy) {
+  aqs_tuning tn{};
+  tn.use_graph = 1;
+  Case k({100, 1100}, tn);   // one workgroup, and tiles
+  k.load_all();
+  R().fail_capture = true;
+  const int32_t rep[2] = {0, 1};
+  expect(aqs_minimize_batch(k.c, 2, rep, AQS_START_PLAIN, nullptr, nullptr, nullptr) == AQS_EHIP, "capture refused");
+  expect(R().launched["k_small"] == 1, "the small slot's launch");
+  if (!destroy) {
+    expect(hipStreamSynchronize(k.stream) == hipSuccess && R().small_pending == 0,
+           "the context's stream did not wait for its side stream");
+  }
+  call(aqs_destroy(k.c), "destroy");
+  expect(R().small_pending == 0 && R().lost_ops == 0, "destroyed with work in flight");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -425,6 +444,8 @@ int main(int argc, char** argv) {
   if (what == "linear_start_polls") linear_start_polls(false);
   else if (what == "linear_start_polls_profiled") linear_start_polls(true);
   else if (what == "slot_loads_wait") slot_loads_wait();
+  else if (what == "side_stream_joins") side_stream_joins(false);
+  else if (what == "side_stream_joins_destroy") side_stream_joins(true);
   else wrong("no such scenario");
   std::printf("ok\n");
   return 0;

@@ -30,7 +30,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["linear_start_polls", "linear_start_polls_profiled", "slot_loads_wait"])
+@pytest.mark.parametrize("scenario", ["linear_start_polls", "linear_start_polls_profiled", "slot_loads_wait",
+                                      "side_stream_joins", "side_stream_joins_destroy"])
 def test_scenario(driver, scenario):
     res = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0 and res.stdout.strip().endswith("ok"), res.stdout + res.stderr
