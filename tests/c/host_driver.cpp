@@ -437,6 +437,20 @@ void side_stream_joins(bool destroy) {
   expect(R().small_pending == 0 && R().lost_ops == 0, "destroyed with work in flight");
 }
 
+// A launch of small slots alone outlasts a minimisation, so that a slow one does
+// not make a batch of extrapolated slots wait for it twice; starts whose lists
+// the host rebuilds end it with the block.
+void small_launch_length(int start, bool many) {
+  aqs_tuning tn{};
+  tn.block_iters = 8;
+  Case k({100, 100, 100}, tn);
+  k.load_all();
+  const int32_t rep[3] = {0, 1, 2}, steps[3] = {3, 3, 3};
+  call(aqs_minimize_batch(k.c, 3, rep, start, steps, nullptr, nullptr), "minimize");
+  for (int n : R().small_iters) expect(many ? n >= 2048 : n == 8, "the length of a launch");
+  call(aqs_destroy(k.c), "destroy");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -446,6 +460,9 @@ int main(int argc, char** argv) {
   else if (what == "slot_loads_wait") slot_loads_wait();
   else if (what == "side_stream_joins") side_stream_joins(false);
   else if (what == "side_stream_joins_destroy") side_stream_joins(true);
+  else if (what == "length_plain") small_launch_length(AQS_START_PLAIN, true);
+  else if (what == "length_extrapolated") small_launch_length(AQS_START_EXTRAPOLATED, true);
+  else if (what == "length_linear") small_launch_length(AQS_START_LINEAR, false);
   else wrong("no such scenario");
   std::printf("ok\n");
   return 0;
