@@ -368,9 +368,11 @@ struct aqs_ctx {
   // once a kernel that writes states is launched (from lane_launch on until the
   // block has been read back, whatever its starts read meanwhile)
   bool synced = false;
-  // pinned staging of atoms and records: each call that uses it waits for the
-  // context stream before it returns
+  // pinned staging of atoms and records (pageable where there is no pinned
+  // memory to be had): each call that uses it waits for the context stream
+  // before it returns
   char* stage = nullptr;
+  std::vector<char> pageable;
   size_t stage_cap = 0;
   std::vector<char> loaded, dirty;
   std::vector<int32_t> tiles_now;  // force tiles of each slot's current grid
@@ -721,17 +723,20 @@ aqs_status pull_state(aqs_ctx* c) {
   return AQS_OK;
 }
 
-// bytes of pinned staging, the caller's until it returns
-aqs_status stage_take(aqs_ctx* c, size_t bytes, void** out) {
-  if (!c->stage) {
+// bytes of staging, the caller's until it returns
+void* stage_take(aqs_ctx* c, size_t bytes) {
+  if (!c->stage && c->pageable.empty()) {
     size_t most = 0;
     for (const Geom& g : c->lo.geom) most = std::max(most, (size_t)g.n * (8 * c->dim + 1));
     c->stage_cap = std::max(most, std::min(kStageBytes, most * c->n_rep));
-    HIPCHK(hipHostMalloc((void**)&c->stage, c->stage_cap, hipHostMallocDefault));
+    if (hipHostMalloc((void**)&c->stage, c->stage_cap, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      c->stage = nullptr;
+    }
   }
-  if (bytes > c->stage_cap) return fail(AQS_ENOMEM, "%zu bytes exceed the pinned staging", bytes);
-  *out = c->stage;
-  return AQS_OK;
+  if (c->stage && bytes <= c->stage_cap) return c->stage;
+  if (c->pageable.size() < bytes) c->pageable.resize(bytes);
+  return c->pageable.data();
 }
 
 // The d components of an atom's values, compacted by atom id in the slot's
@@ -739,9 +744,7 @@ aqs_status stage_take(aqs_ctx* c, size_t bytes, void** out) {
 aqs_status read_atoms(aqs_ctx* c, int32_t rep, const double* packed, double* out) {
   const Geom& g = c->lo.geom[rep];
   const size_t bytes = sizeof(double) * (size_t)g.n * c->dim;
-  void* buf = nullptr;
-  aqs_status st = stage_take(c, bytes, &buf);
-  if (st) return st;
+  void* buf = stage_take(c, bytes);
   HIPCHK(hipMemcpyAsync(buf, packed, bytes, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   std::memcpy(out, buf, bytes);
@@ -1347,17 +1350,7 @@ aqs_status finish_chains(aqs_ctx* c, const std::vector<int32_t>& sel, const int3
   if (!records) return AQS_OK;
   const int stride = max_steps + 1;
   // the slots' records, one wait for all of them
-  std::vector<StepRecord> pageable;
-  const size_t bytes = sizeof(StepRecord) * (size_t)n_sel * stride;
-  void* buf = nullptr;
-  if (c->stage && bytes <= c->stage_cap) {
-    st = stage_take(c, bytes, &buf);
-    if (st) return st;
-  } else {
-    pageable.resize((size_t)n_sel * stride);
-    buf = pageable.data();
-  }
-  StepRecord* tmp = static_cast<StepRecord*>(buf);
+  StepRecord* tmp = static_cast<StepRecord*>(stage_take(c, sizeof(StepRecord) * (size_t)n_sel * stride));
   for (int i = 0; i < n_sel; ++i)
     if (done[i] > 0)
       HIPCHK(hipMemcpyAsync(tmp + (size_t)i * stride, c->log + (int64_t)sel[i] * c->tn.log_cap,
@@ -1616,9 +1609,7 @@ aqs_status aqs_set_replica(aqs_ctx* c, int32_t rep, const uint8_t* types, const 
   // the caller's arrays through pinned staging into the slot's scratch, where a
   // kernel spreads them into the device's layout
   const size_t xb = sizeof(double) * (size_t)g.n * c->dim, bytes = xb + (size_t)g.n;
-  void* buf = nullptr;
-  st = stage_take(c, bytes, &buf);
-  if (st) return st;
+  void* buf = stage_take(c, bytes);
   std::memcpy(buf, pos, xb);
   std::memcpy((char*)buf + xb, types, (size_t)g.n);
   char* raw = reinterpret_cast<char*>(c->tpos4 + g.atom_off);

@@ -451,6 +451,23 @@ void small_launch_length(int start, bool many) {
   call(aqs_destroy(k.c), "destroy");
 }
 
+// No pinned memory left for the staging: atoms and records still get through.
+void staging_without_pinned_memory() {
+  Case k({100, 100});
+  R().fail_pinned = true;
+  k.load_all();
+  const int32_t rep[2] = {0, 1}, steps[2] = {2, 2};
+  aqs_step_record rec[6];
+  for (aqs_step_record& r : rec) r.status = 7;
+  call(aqs_minimize_batch(k.c, 2, rep, AQS_START_PLAIN, steps, nullptr, rec), "minimize");
+  expect(rec[5].status == 0, "the last record");
+  std::vector<double> x(200);
+  call(aqs_get_positions(k.c, 1, x.data()), "get_positions");
+  expect(x == k.pos[1], "the positions as they were loaded");
+  expect(hipGetLastError() == hipSuccess, "an error left behind");
+  call(aqs_destroy(k.c), "destroy");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -463,6 +480,7 @@ int main(int argc, char** argv) {
   else if (what == "length_plain") small_launch_length(AQS_START_PLAIN, true);
   else if (what == "length_extrapolated") small_launch_length(AQS_START_EXTRAPOLATED, true);
   else if (what == "length_linear") small_launch_length(AQS_START_LINEAR, false);
+  else if (what == "staging_without_pinned_memory") staging_without_pinned_memory();
   else wrong("no such scenario");
   std::printf("ok\n");
   return 0;
