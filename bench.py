@@ -183,6 +183,19 @@ def train_on_history(eng, star, spare, steps, epochs, seed, dim):
                    "loss_last": float(hist[-1])}
 
 
+def launch_times(cnt: dict, dim: int) -> dict:
+    """Timed launches of the kernel that evaluates the forces: k_force, or
+    k_small where the slots are small 2D ones that run whole iterations in one
+    workgroup (atoms_per_launch then over all iterations of a launch)."""
+    small = cnt["small_timed"] > 0 and cnt["force_timed"] == 0
+    n = cnt["small_timed" if small else "force_timed"]
+    ms, evals = (cnt["small_ms"], cnt["small_timed_atom_evals"]) if small else \
+        (cnt["force_ms"], cnt["timed_atom_evals"])
+    return {"kernel": "k_small" if small else f"k_force<{dim}>", "avg_launch_ms": ms / n if n else 0.0,
+            "timed_launches": n, "atoms_per_launch": evals / n if n else 0.0,
+            "update_avg_ms": cnt["update_ms"] / cnt["update_timed"] if cnt["update_timed"] else None}
+
+
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
@@ -386,24 +399,24 @@ def main() -> int:
     # driver lanes with live checks)
     cnt = head["counters"]
     flops_per_atom = 0.5 * nb * FLOPS_PER_PAIR
-    n_timed = cnt["force_timed"]
-    avg_ms = cnt["force_ms"] / n_timed if n_timed else 0.0
-    atoms_per_launch = cnt["timed_atom_evals"] / n_timed if n_timed else 0.0
+    lt = launch_times(cnt, dim)
+    n_timed, avg_ms, atoms_per_launch = lt["timed_launches"], lt["avg_launch_ms"], lt["atoms_per_launch"]
+
+    def traffic_of(t):
+        return force_traffic(dim, t["atoms_per_launch"]) if t["kernel"] != "k_small" else None
     achieved_tflops = flops_per_atom * atoms_per_launch / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else None
     achieved_gbs = FORCE_BYTES_PER_ATOM[dim] * atoms_per_launch / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else None
-    traffic = force_traffic(dim, atoms_per_launch)
+    traffic = traffic_of(lt)
     kernel_form = None
     if "kernel" in forms:
-        kc = forms["kernel"]["counters"]
-        kms = kc["force_ms"] / kc["force_timed"]
-        katoms = kc["timed_atom_evals"] / kc["force_timed"]
+        kt = launch_times(forms["kernel"]["counters"], dim)
+        kms, katoms = kt["avg_launch_ms"], kt["atoms_per_launch"]
         ktf = flops_per_atom * katoms / (kms * 1e-3) / 1e12
-        kernel_form = {"kernel": f"k_force<{dim}>", "avg_launch_ms": kms, "timed_launches": kc["force_timed"],
+        kernel_form = {"kernel": kt["kernel"], "avg_launch_ms": kms, "timed_launches": kt["timed_launches"],
                        "atoms_per_launch": katoms, "achieved_tflops": ktf, "frac_fp64": ktf / FP64_PEAK_TFLOPS,
                        "hbm_gbs_algorithmic": FORCE_BYTES_PER_ATOM[dim] * katoms / (kms * 1e-3) / 1e9,
-                       "traffic_bytes_per_atom": (force_traffic(dim, katoms) / katoms)
-                       if force_traffic(dim, katoms) else None,
-                       "update_avg_ms": kc["update_ms"] / kc["update_timed"],
+                       "traffic_bytes_per_atom": traffic_of(kt) / katoms if traffic_of(kt) else None,
+                       "update_avg_ms": kt["update_avg_ms"],
                        "round": f"plain start, batched (no live checks), P={P} x K={args.kernel_K}, "
                                 f"every force launch timed"}
     comparison = None
@@ -463,7 +476,7 @@ def main() -> int:
         "roofline": {"bound": "alu", "achieved": achieved_tflops, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved_tflops / FP64_PEAK_TFLOPS if achieved_tflops else None,
                      "traffic": traffic,
-                     "kernel": f"k_force<{dim}>", "avg_launch_ms": avg_ms, "timed_launches": n_timed,
+                     "kernel": lt["kernel"], "avg_launch_ms": avg_ms, "timed_launches": n_timed,
                      "atoms_per_launch": atoms_per_launch,
                      "algorithmic_flops_per_atom": flops_per_atom,
                      "algorithmic_bytes_per_atom": FORCE_BYTES_PER_ATOM[dim],

@@ -429,11 +429,26 @@ typedef struct {
   int64_t timed_atom_evals; /* ... over the force launches timed (force_timed) */
 } aqs_counters;
 
+/* Launches of the kernel that runs whole iterations (force, control and move,
+ * and lists of its own) of small 2D slots, one workgroup per slot: their
+ * evaluations and list rebuilds count in aqs_counters, their launches and times
+ * here only. */
+typedef struct {
+  double ms;                /* summed duration of the timed launches */
+  int64_t timed;            /* launches timed */
+  int64_t launches;         /* launches issued */
+  int64_t timed_atom_evals; /* atoms whose force the timed launches evaluated */
+} aqs_small_counters;
+
 /* Time every n-th block of FIRE iterations (0 = no timing), on every
  * driver lane's stream (aqs_run_round with live = 1 has two). */
 aqs_status aqs_set_profiling(aqs_ctx* ctx, int32_t every_nth_block);
 
 aqs_status aqs_get_counters(aqs_ctx* ctx, aqs_counters* out, int32_t reset);
+
+/* The same of small slots' launches; a reset of aqs_get_counters resets these
+ * too.  Synchronises. */
+aqs_status aqs_get_small_counters(aqs_ctx* ctx, aqs_small_counters* out);
 
 /* ------------------------------------------------------------------------
  * Learned start (the paper starts every minimisation at F r, Eq. 12, and

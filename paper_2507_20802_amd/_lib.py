@@ -68,6 +68,11 @@ class aqs_counters(ctypes.Structure):
                 ("timed_atom_evals", ctypes.c_int64)]
 
 
+class aqs_small_counters(ctypes.Structure):
+    _fields_ = [("ms", ctypes.c_double), ("timed", ctypes.c_int64), ("launches", ctypes.c_int64),
+                ("timed_atom_evals", ctypes.c_int64)]
+
+
 class aqs_mlp(ctypes.Structure):
     _fields_ = [("dim", ctypes.c_int32), ("pad_", ctypes.c_int32),
                 ("w1", ctypes.c_float * (64 * 128)), ("b1", ctypes.c_float * 128),
@@ -120,6 +125,7 @@ SIGNATURES = {
     "aqs_set_linear_start": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_double, ctypes.c_double]),
     "aqs_set_minimizer": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(aqs_cg_params)]),
     "aqs_get_counters": (ctypes.c_int32, [ctypes.c_void_p, ctypes.POINTER(aqs_counters), ctypes.c_int32]),
+    "aqs_get_small_counters": (ctypes.c_int32, [ctypes.c_void_p, ctypes.POINTER(aqs_small_counters)]),
     "aqs_learned_load": (ctypes.c_int32, [ctypes.c_void_p, ctypes.POINTER(aqs_mlp)]),
     "aqs_learned_features": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]),
     "aqs_learned_predict": (ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]),

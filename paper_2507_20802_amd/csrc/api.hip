@@ -256,7 +256,7 @@ aqs_status make_layout(const aqs_potential* pot, const Tune& tn, int n_rep, cons
   for (int a = 0; a < 3; ++a) lo.o_tdl[a] = take(sizeof(double) * A);
   lo.o_alt4 = take(sizeof(double4) * A);
   lo.o_talt4 = take(sizeof(double4) * A);
-  lo.o_evals = take(3 * sizeof(unsigned long long));   // all evaluations, timed ones; k_small's rebuilds
+  lo.o_evals = take(4 * sizeof(unsigned long long));   // all evaluations, timed ones; k_small's rebuilds, timed evaluations
   lo.o_xref4 = take(sizeof(double4) * A);
   lo.o_zbuf = take(sizeof(uint16_t) * kFeat * A);
   lo.o_lpart = take(sizeof(double) * kLearnParts * ((size_t)lo.blocks + 8));
@@ -383,6 +383,7 @@ struct aqs_ctx {
   int32_t prof_every = 0;
   int64_t block_count = 0;
   aqs_counters cnt{};
+  aqs_small_counters small_cnt{};
 };
 
 namespace {
@@ -1039,12 +1040,13 @@ aqs_status small_launch(aqs_ctx* c, Lane& L, const IterArgs& a, int32_t start_mo
   sa.rebuild = (start_mode == AQS_START_PLAIN || start_mode == AQS_START_EXTRAPOLATED) ? 1 : 0;
   sa.overflow = L.overflow;
   sa.rebuilds = c->evals + 2;
+  if (a.tevals) sa.it.tevals = c->evals + 3;
   if (a.tevals)
     for (hipEvent_t& e : L.small_ev)
       if (!e) HIPCHK(hipEventCreate(&e));
   HIPCHK(launch_small(sa, L.nhalf, L.nsmall - L.nhalf, s, a.tevals ? L.small_ev[0] : nullptr, a.tevals ? L.small_ev[1] : nullptr));
   L.small_timed = a.tevals != nullptr;
-  ++c->cnt.force_launches;
+  ++c->small_cnt.launches;
   return AQS_OK;
 }
 
@@ -1268,11 +1270,11 @@ aqs_status lane_poll(aqs_ctx* c, Lane& L, bool all_states, int& active) {
     c->cnt.update_timed += M;
     L.timed = false;
   }
-  if (L.small_timed) {   // whole iterations: counted as force time
+  if (L.small_timed) {
     float f = 0.f;
     HIPCHK(hipEventElapsedTime(&f, L.small_ev[0], L.small_ev[1]));
-    c->cnt.force_ms += f;
-    ++c->cnt.force_timed;
+    c->small_cnt.ms += f;
+    ++c->small_cnt.timed;
     L.small_timed = false;
   }
   note_block(c, L);
@@ -2239,7 +2241,7 @@ aqs_status aqs_set_profiling(aqs_ctx* c, int32_t every_nth_block) {
 
 aqs_status aqs_get_counters(aqs_ctx* c, aqs_counters* out, int32_t reset) {
   if (!c) return fail(AQS_EINVAL, "null context");
-  unsigned long long ev[3] = {0, 0, 0};
+  unsigned long long ev[4] = {0, 0, 0, 0};
   HIPCHK(hipMemcpyAsync(ev, c->evals, sizeof ev, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   c->cnt.atom_evals = (int64_t)ev[0] + c->lin_evals;
@@ -2250,10 +2252,21 @@ aqs_status aqs_get_counters(aqs_ctx* c, aqs_counters* out, int32_t reset) {
   }
   if (reset) {
     c->cnt = aqs_counters{};
+    c->small_cnt = aqs_small_counters{};
     c->lin_evals = 0;
     HIPCHK(hipMemsetAsync(c->evals, 0, sizeof ev, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
   }
+  return AQS_OK;
+}
+
+aqs_status aqs_get_small_counters(aqs_ctx* c, aqs_small_counters* out) {
+  if (!c || !out) return fail(AQS_EINVAL, "null argument");
+  unsigned long long ev = 0;
+  HIPCHK(hipMemcpyAsync(&ev, c->evals + 3, sizeof ev, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  *out = c->small_cnt;
+  out->timed_atom_evals = (int64_t)ev;
   return AQS_OK;
 }
 

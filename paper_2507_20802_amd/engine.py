@@ -377,9 +377,11 @@ class Engine:
         check(self._lib.aqs_set_profiling(self._ctx, int(every_nth_block)), "aqs_set_profiling")
 
     def counters(self, reset: bool = False) -> dict:
-        c = _lib.aqs_counters()
+        """The library's counters; those of small slots' launches as small_*."""
+        c, s = _lib.aqs_counters(), _lib.aqs_small_counters()
+        check(self._lib.aqs_get_small_counters(self._ctx, ctypes.byref(s)), "aqs_get_small_counters")
         check(self._lib.aqs_get_counters(self._ctx, ctypes.byref(c), int(reset)), "aqs_get_counters")
-        return {k: getattr(c, k) for k, _ in c._fields_}
+        return {**{k: getattr(c, k) for k, _ in c._fields_}, **{f"small_{k}": getattr(s, k) for k, _ in s._fields_}}
 
     # -- learned start ----------------------------------------------------
     def _dev_f32(self, rows: int, cols: int, out=None):
