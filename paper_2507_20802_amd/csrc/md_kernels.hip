@@ -289,50 +289,37 @@ __device__ __forceinline__ void packed_segment(const double4 pi, __amdgpu_buffer
   }
 }
 
-// A lane's share of an atom's packed list (engine.h), TPA lanes per atom: lane
-// sub takes the A groups sub, sub + TPA, ... from group row 0 up and the B
-// groups from group row G - 1 - sub down (G = max_nb / 4).  The first group of
-// each is requested at once: rows 0 .. TPA - 1 and G - TPA .. G - 1 exist
-// whatever the counts are, which may still be in flight.
-template <int TPA>
-struct PackedList {
-  __amdgpu_buffer_rsrc_t rs;
-  uint32_t step, lba, lbb, sbb;
-  int gcap;
-  __device__ __forceinline__ PackedList(const uint2* Lp, int col, int npad, int max_nb) {
-    const int sub = (int)(threadIdx.x % TPA);
-    const int G = max_nb / kGroup;
-    // group row of step k: A  k TPA + sub,  B  (G - TPA - k TPA) + (TPA - 1 - sub)
-    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint2*>(Lp), (short)0,
-                                           (int)(8u * (uint32_t)npad * (uint32_t)G), kBufferFlags);
-    const uint32_t row_bytes = 8u * (uint32_t)npad;
-    step = (uint32_t)TPA * row_bytes;
-    lba = 8u * (uint32_t)col + (uint32_t)sub * row_bytes;
-    lbb = 8u * (uint32_t)col + (uint32_t)(TPA - 1 - sub) * row_bytes;
-    sbb = (uint32_t)(G - TPA) * row_bytes;
-    gcap = G / TPA;
-  }
-  __device__ __forceinline__ uint2 first_a() const { return packed_group(rs, lba, 0u, step, 0, gcap); }
-  __device__ __forceinline__ uint2 first_b() const { return packed_group(rs, lbb, sbb, 0u - step, 0, gcap); }
-};
-
-// Lennard-Jones sum of one atom over its packed list.
+// Lennard-Jones sum of one atom over its packed list (engine.h), TPA lanes
+// per atom: lane sub takes the A groups sub, sub + TPA, ... from group row 0
+// up and the B groups from group row G - 1 - sub down (G = max_nb / 4).
 template <int D, bool WE, int TPA>
-__device__ __forceinline__ void atom_pairs_packed(const double4 pi, int ti, const PackedList<TPA>& L,
-                                                  uint2 first_a, uint2 first_b, int32_t counts,
+__device__ __forceinline__ void atom_pairs_packed(const double4 pi, int ti, const uint2* Lp, int col,
+                                                  int npad, int32_t counts, int max_nb,
                                                   const double* hx, const double* hy,
                                                   const double* hz, const PairParams* pp,
                                                   double& fx, double& fy, double& fz, double& e,
                                                   double& w) {
   const int sub = (int)(threadIdx.x % TPA);
+  const int G = max_nb / kGroup;
   const int na = counts & 0xffff, nb = (counts >> 16) & 0xffff;
   const int ga = (na + kGroup - 1) / kGroup, gb = (nb + kGroup - 1) / kGroup;
+  const int gcap = G / TPA;
   const int my_a = ga > sub ? (ga - sub + TPA - 1) / TPA : 0;
   const int my_b = gb > sub ? (gb - sub + TPA - 1) / TPA : 0;
-  packed_segment<D, WE>(pi, L.rs, L.lba, 0u, L.step, my_a, L.gcap, first_a, pp[2 * ti], hx, hy, hz, fx,
-                        fy, fz, e, w);
-  packed_segment<D, WE>(pi, L.rs, L.lbb, L.sbb, 0u - L.step, my_b, L.gcap, first_b, pp[2 * ti + 1], hx,
-                        hy, hz, fx, fy, fz, e, w);
+  // group row of step k: A  k TPA + sub,  B  (G - TPA - k TPA) + (TPA - 1 - sub)
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint2*>(Lp), (short)0, (int)(8u * (uint32_t)npad * (uint32_t)G), kBufferFlags);
+  const uint32_t row_bytes = 8u * (uint32_t)npad;
+  const uint32_t step = (uint32_t)TPA * row_bytes;
+  const uint32_t lba = 8u * (uint32_t)col + (uint32_t)sub * row_bytes;
+  const uint32_t lbb = 8u * (uint32_t)col + (uint32_t)(TPA - 1 - sub) * row_bytes;
+  const uint32_t sbb = (uint32_t)(G - TPA) * row_bytes;
+  const uint2 first_a = my_a > 0 ? packed_group(rs, lba, 0u, step, 0, gcap) : make_uint2(0u, 0u);
+  const uint2 first_b = my_b > 0 ? packed_group(rs, lbb, sbb, 0u - step, 0, gcap) : make_uint2(0u, 0u);
+  packed_segment<D, WE>(pi, rs, lba, 0u, step, my_a, gcap, first_a, pp[2 * ti], hx, hy, hz, fx, fy,
+                        fz, e, w);
+  packed_segment<D, WE>(pi, rs, lbb, sbb, 0u - step, my_b, gcap, first_b, pp[2 * ti + 1], hx, hy, hz,
+                        fx, fy, fz, e, w);
   combine_lanes<D, WE, TPA>(fx, fy, fz, e, w);
 }
 
@@ -687,53 +674,25 @@ __device__ __forceinline__ void control(const IterArgs& a, int rep, const Geom& 
 // the per-block partials (E, |F|^2, F.v, |v|^2, max |F_i|^2, W_xy, non-finite)
 // and, in the last block of each slot, the FIRE control.
 
-// What an atom's sum needs from memory besides the halo: its index in the slot
-// and list lengths (begin), then its position and first groups (rest).  The
-// force kernel requests the begin of the block's first atoms beside the halo's
-// indices and both first groups with the position, so they cost two round
-// trips less, 7 % of a launch that leaves the chip idle (12.1 us for 1501 atoms
-// in 3D, 9.9 for 4 x 2100 in 2D).  The rest beside the halo's positions does not
-// fit in the registers: with velocities it spilled and took 14.1 and 11.1 us.
-struct AtomAhead {
-  int li;
-  int32_t counts;
-  double4 p;
-  uint2 a, b;
-};
-__device__ __forceinline__ void ahead_begin(const IterArgs& a, const Geom& g, int col, AtomAhead& x) {
-  x.li = a.tord[g.atom_off + col];
-  x.counts = a.nbc[g.atom_off + col];
-}
-template <int D, int TPA, bool LDS>
-__device__ __forceinline__ void ahead_rest(const IterArgs& a, const Geom& g, int col, AtomAhead& x) {
-  const int64_t gi = g.atom_off + x.li;
-  x.p = a.pos4[gi];
-  if (LDS) {
-    const PackedList<TPA> L(a.nbp + g.nb_off / kGroup, col, g.npad, a.max_nb);
-    x.a = L.first_a();
-    x.b = L.first_b();
-  }
-}
-
-// Force of one atom of the tile (TPA lanes), accumulated into the thread's
-// partials: E, |F|^2, F.v, |v|^2 (conjugate gradients: F.F0, F0 the force at
-// the line-search origin), max |F_i|^2, W_xy, non-finite, max |v_i|^2.
+// Force of one atom li of the tile (TPA lanes), accumulated into the
+// thread's partials: E, |F|^2, F.v, |v|^2 (conjugate gradients: F.F0, F0 the
+// force at the line-search origin), max |F_i|^2, W_xy, non-finite, max |v_i|^2.
 template <int D, bool WE, int TPA, bool LDS>
-__device__ __forceinline__ void force_atom(const IterArgs& a, const Geom& g, const AtomAhead& x, int col,
+__device__ __forceinline__ void force_atom(const IterArgs& a, const Geom& g, int li, int col,
                                            const double (*sh)[4], const PairParams* spp,
                                            const double* hx, const double* hy, const double* hz,
                                            bool cg, double* part) {
-  const int64_t gi = g.atom_off + x.li;
-  const double4 pi = x.p;
+  const int64_t gi = g.atom_off + li;
+  const double4 pi = a.pos4[gi];
   double fx = 0.0, fy = 0.0, fz = 0.0, e = 0.0, w = 0.0;
   if (LDS)
-    atom_pairs_packed<D, WE, TPA>(pi, (int)pi.w,
-                                  PackedList<TPA>(a.nbp + g.nb_off / kGroup, col, g.npad, a.max_nb), x.a,
-                                  x.b, x.counts, hx, hy, hz, spp, fx, fy, fz, e, w);
+    atom_pairs_packed<D, WE, TPA>(pi, (int)pi.w, a.nbp + g.nb_off / kGroup, col, g.npad,
+                                  a.nbc[g.atom_off + col], a.max_nb, hx, hy, hz, spp, fx, fy, fz,
+                                  e, w);
   else
-    atom_pairs<D, WE, TPA>(pi, (int)pi.w, a.nbl + g.nb_off, col, g.npad, x.counts, a.max_nb,
-                           (uint32_t)x.li | (13u << kCodeShift), a.pos4 + g.atom_off, sh, spp, fx,
-                           fy, fz, e, w);
+    atom_pairs<D, WE, TPA>(pi, (int)pi.w, a.nbl + g.nb_off, col, g.npad, a.nbc[g.atom_off + col],
+                           a.max_nb, (uint32_t)li | (13u << kCodeShift), a.pos4 + g.atom_off, sh,
+                           spp, fx, fy, fz, e, w);
   if (threadIdx.x % TPA != 0) return;
   a.fx[gi] = fx;
   a.fy[gi] = fy;
@@ -754,17 +713,16 @@ __device__ __forceinline__ void force_atom(const IterArgs& a, const Geom& g, con
   part[7] = fmax(part[7], vv);
 }
 
-// The tile's atoms; x: the thread's first one, requested by the caller.
 template <int D, bool WE, int TPA, bool LDS>
-__device__ __forceinline__ void force_tile(const IterArgs& a, const Geom& g, int a0, int a1, AtomAhead x,
+__device__ __forceinline__ void force_tile(const IterArgs& a, const Geom& g, int a0, int a1,
                                            const double (*sh)[4], const PairParams* spp,
                                            const double* hx, const double* hy, const double* hz,
                                            bool cg, double* part) {
   constexpr int per = kBlock / TPA;
-  for (int k = a0 + (int)(threadIdx.x / TPA); k < a1; k += per) {
-    if (k >= a0 + per) ahead_begin(a, g, k, x);
-    ahead_rest<D, TPA, LDS>(a, g, k, x);
-    force_atom<D, WE, TPA, LDS>(a, g, x, k, sh, spp, hx, hy, hz, cg, part);
+  for (int b = a0; b < a1; b += per) {
+    const int k = b + (int)(threadIdx.x / TPA);
+    if (k < a1)
+      force_atom<D, WE, TPA, LDS>(a, g, a.tord[g.atom_off + k], k, sh, spp, hx, hy, hz, cg, part);
   }
 }
 
@@ -818,10 +776,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W))) voi
   const bool compute = phase_force(phase);
   if (!compute || tix - g.tile_off >= ntiles) return;
   const bool cg = (phase == PH_CG);
-  const int col0 = hdr.a0 + tid / TPA;   // this thread's first atom
-  AtomAhead x;
-  x.li = -1;
-  if (col0 < hdr.a1) ahead_begin(a, g, col0, x);
 
   __shared__ double hx[CAP];
   __shared__ double hy[CAP];
@@ -846,14 +800,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W))) voi
       }
       __syncthreads();
       if (we)
-        force_tile<D, true, TPA, true>(a, g, hdr.a0, hdr.a1, x, sh, spp, hx, hy, hz, cg, part);
+        force_tile<D, true, TPA, true>(a, g, hdr.a0, hdr.a1, sh, spp, hx, hy, hz, cg, part);
       else
-        force_tile<D, false, TPA, true>(a, g, hdr.a0, hdr.a1, x, sh, spp, hx, hy, hz, cg, part);
+        force_tile<D, false, TPA, true>(a, g, hdr.a0, hdr.a1, sh, spp, hx, hy, hz, cg, part);
     } else {
       if (we)
-        force_tile<D, true, TPA, false>(a, g, hdr.a0, hdr.a1, x, sh, spp, hx, hy, hz, cg, part);
+        force_tile<D, true, TPA, false>(a, g, hdr.a0, hdr.a1, sh, spp, hx, hy, hz, cg, part);
       else
-        force_tile<D, false, TPA, false>(a, g, hdr.a0, hdr.a1, x, sh, spp, hx, hy, hz, cg, part);
+        force_tile<D, false, TPA, false>(a, g, hdr.a0, hdr.a1, sh, spp, hx, hy, hz, cg, part);
     }
     block_reduce<kForceParts>(part, ops, red);
     if (tid == 0) {
