@@ -1320,22 +1320,20 @@ __global__ __launch_bounds__(T) void k_small(SmallArgs sa) {
   int na = 0, nb = 0;   // this lane's entries of either type
   bool rebuilt = false;
 
-  // The list, from the positions x_ref at the last build.
+  // The list, from the positions x_ref at the last build (which S.x holds
+  // meanwhile), in FP64: a coordinate in a long box has few FP32 digits left for
+  // a distance.
   auto build = [&]() {
     const Box b = box_at(g, S.ss.k_build);
-    float2* xf = reinterpret_cast<float2*>(S.x);
-    if (lead) xf[me] = make_float2((float)x0.x, (float)x0.y);
+    if (lead) S.x[me] = x0;
     for (int c = tid; c <= kSmallCells; c += T) S.cstart[c] = 0;
     for (int c = tid; c < kSmallCells; c += T) S.aend[c] = 0;
     // every entry the filling: what is not written below is beyond every cutoff
     const uint32_t fill = (uint32_t)min(me, n - 1) | ((uint32_t)kSmallFar << kSmallCode);
     for (int row = 0; row < kSmallRows; ++row) S.list[row][tid] = fill | (fill << 16);
     const double det = b.h00 * b.h11 - b.h01 * b.h10;
-    const float i00 = (float)(b.h11 / det), i01 = (float)(-b.h01 / det), i10 = (float)(-b.h10 / det),
-                i11 = (float)(b.h00 / det);
-    const float h00 = (float)b.h00, h01 = (float)b.h01, h10 = (float)b.h10, h11 = (float)b.h11;
-    const float xi = (float)x0.x, yi = (float)x0.y;
-    // cells at least a list distance wide (the margin of the FP32 test with it)
+    const double i00 = b.h11 / det, i01 = -b.h01 / det, i10 = -b.h10 / det, i11 = b.h00 / det;
+    // cells at least a list distance wide (the margin of the test with it)
     int nc0, nc1;
     {
       const double rl = a.rc_max + a.skin + 2.0 * kListMargin;
@@ -1351,7 +1349,7 @@ __global__ __launch_bounds__(T) void k_small(SmallArgs sa) {
     // counting sort of the atoms into the cells
     int c0 = 0, c1 = 0;
     if (mine) {
-      const float s0 = i00 * xi + i01 * yi, s1 = i10 * xi + i11 * yi;
+      const double s0 = i00 * x0.x + i01 * x0.y, s1 = i10 * x0.x + i11 * x0.y;
       c0 = min(max((int)(s0 * nc0), 0), nc0 - 1);
       c1 = min(max((int)(s1 * nc1), 0), nc1 - 1);
     }
@@ -1392,7 +1390,7 @@ __global__ __launch_bounds__(T) void k_small(SmallArgs sa) {
     int total[2];
     for (int tj = 0; tj < 2; ++tj) {
       const double rc = sqrt(S.pp[2 * ti + tj].rc2) + a.skin;
-      const float thr = (float)((rc + kListMargin) * (rc + kListMargin));
+      const double thr = (rc + kListMargin) * (rc + kListMargin);   // the tiles' lists
       // entry k of lane l of the atom, below the lane's entries of type A
       auto put = [&](int l, int k, uint32_t e) {
         const int row = k / 2 + (tj == 0 ? 0 : ((total[0] - l + tpa - 1) / tpa + 1) / 2);
@@ -1409,12 +1407,12 @@ __global__ __launch_bounds__(T) void k_small(SmallArgs sa) {
           for (int qq = 0; __any(mine && q0 + qq < q1); qq += tpa) {
             const bool in = mine && q0 + qq + sub < q1;
             const int j = in ? (int)S.order[q0 + qq + sub] : 0;
-            const float2 q = xf[j];
-            float dx = q.x - xi, dy = q.y - yi;
+            const double2 q = S.x[j];
+            double dx = q.x - x0.x, dy = q.y - x0.y;
             // nearest image: H (s - rint s), its code from -rint s
-            const float nx = rintf(i00 * dx + i01 * dy), ny = rintf(i10 * dx + i11 * dy);
-            dx -= h00 * nx + h01 * ny;
-            dy -= h10 * nx + h11 * ny;
+            const double nx = rint(i00 * dx + i01 * dy), ny = rint(i10 * dx + i11 * dy);
+            dx -= b.h00 * nx + b.h01 * ny;
+            dy -= b.h10 * nx + b.h11 * ny;
             const bool hit = in && j != me && dx * dx + dy * dy < thr;
             const unsigned long long m = __ballot(hit) & group;
             const int idx = base + __popcll(m & below);
