@@ -260,15 +260,27 @@ __global__ __launch_bounds__(kBlock) void k_rb_back(RebuildArgs a) {
 // every atom and sent each entry to memory twice, one by one.  Rebuild of 16 x
 // 32768 atoms (3D, up to 16 of them at once): 535 us, 2246 before; of one
 // replica 67, 256 before.
+// "Cell" above is a group of neighbouring cells of the row where a tile spans
+// more of them than the tables below hold (short cutoffs, tiles filled to the
+// limit): the group's atoms share the candidates around it.
 // A tile whose compact halo does not fit in the force kernel's LDS gets word
 // lists (j | code); so does a tile past the limits below, tested in FP64
-// straight from the cells (kernel's end).
+// straight from the cells (kernel's end), and a wide tile of a slot with fewer
+// than two atoms per cell.  There the halo hardly shortens a force launch, and
+// the search takes less time: 2D, 159048 atoms, cutoff 2.5, list kernel and
+// useful force launch, groups against search: 92 and 11.0 us, 61 and 10.9 at 0.8
+// atoms per cell; 88 and 8.1 us, 50 and 9.5 at 2.4, where lists that live over
+// about 25 iterations pay for the groups.
 constexpr int kListBlock = 512;     // threads of the list kernel
 constexpr int kChunkParts = 2;      // a unit's chunks are split over this many wavefronts
 constexpr int kUnitAtoms = 16;      // atoms of one cell that a wavefront tests together
-constexpr int kListCells = 96;      // cells a tile may span
-constexpr int kCellChunks = 32;     // chunks of one cell's candidates
-constexpr int kTileChunks = 128;    // ... of all the tile's cells
+constexpr int kListCells = 96;      // groups of cells in a tile
+constexpr int kTileChunks = 128;    // chunks of all their candidates
+// Cells of a group at first (the chunks may ask for four times as many): FP32
+// offsets within it, a few hundred list distances, round far below kListMargin.
+// A tile of more cells than 96 such groups goes to the FP64 search.
+constexpr int kGroupCells = 128;
+static_assert(kTileChunks >= kCandCap / kWave, "one group of all candidates fits");
 constexpr int kMaskWords = 2048;    // masks kept at once; larger tiles go in batches of atoms
 
 // Inclusive sum over the lanes of a wavefront.
@@ -340,14 +352,19 @@ __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4)))
     s_cx1 = 0;
   }
   __syncthreads();
-  if (nt > 0)
-    for (int x = tid; x < nc[0]; x += kListBlock) {
-      const int b = cs[row0 + x], e = cs[row0 + x + 1];
-      if (b <= a0 && a0 < e) s_cx0 = x;
-      if (b < a1 && a1 <= e) s_cx1 = x;
+  if (nt > 0 && nc[0] <= kListBlock) {
+    if (tid < nc[0]) {
+      const int b = cs[row0 + tid], e = cs[row0 + tid + 1];
+      if (b <= a0 && a0 < e) s_cx0 = tid;
+      if (b < a1 && a1 <= e) s_cx1 = tid;
     }
+  } else if (nt > 0 && tid < 2) {   // a longer row: where its first and last atom were binned
+    int c3[3];
+    cell_of_pos<D>(bx, nc, P[tid == 0 ? a0 : a1 - 1], c3);
+    (tid == 0 ? s_cx0 : s_cx1) = c3[0];
+  }
   __syncthreads();
-  const int cx0 = s_cx0, ncell = s_cx1 - s_cx0 + 1;
+  const int cx0 = s_cx0, row_cells = s_cx1 - s_cx0 + 1;
   if (tid < kRuns) {
     runs[tid] = make_run<D>(tid, cx0, s_cx1, cy, cz, nc, cs);
     code_shift(tid, bx, s_sh[tid]);
@@ -372,15 +389,24 @@ __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4)))
   }
   __syncthreads();
   const int ncand = s_ncand;
-  bool fast = st->list_mode == 0 && ncand <= kCandCap && nt <= kTileSort && ncell <= kListCells;
-  // the cells' ranges
-  if (fast) {
-    for (int ci = tid; ci <= ncell; ci += kListBlock) s_cs[ci] = cs[row0 + cx0 + ci];
+  const bool fast = st->list_mode == 0 && ncand <= kCandCap && nt <= kTileSort &&
+                    (row_cells <= kListCells ||
+                     (g.n >= 2 * nc[0] * nc[1] * nc[2] && row_cells <= kListCells * kGroupCells));
+  // The groups' ranges: groups of one cell, mostly; of as many as it takes for the
+  // tables to hold them and their chunks (a single group's always fit).
+  int gw = 1, ncell = 1;
+  if (row_cells > kListCells)   // ... and about a unit's atoms each, whose candidates mostly fit in one chunk
+    gw = max((row_cells + kListCells - 1) / kListCells,
+             min(kGroupCells, (kUnitAtoms * row_cells + nt - 1) / max(nt, 1)));
+  while (fast) {
+    ncell = (row_cells + gw - 1) / gw;
+    for (int ci = tid; ci <= ncell; ci += kListBlock) s_cs[ci] = cs[row0 + cx0 + min(ci * gw, row_cells)];
     for (int e = tid; e < ncell * R; e += kListBlock) {
-      const int ci = e / R, q = e % R, cx = cx0 + ci, r = 3 * (q + R0), c0 = s_c0[q + R0];
+      const int ci = e / R, q = e % R, r = 3 * (q + R0), c0 = s_c0[q + R0];
+      const int cx = cx0 + ci * gw, cl = cx0 + min((ci + 1) * gw, row_cells) - 1;   // its first and last cell
       const TileRun m = runs[r + 1];
       s_lo[ci][q] = (uint16_t)(cx > 0 ? m.off + (cs[c0 + cx - 1] - m.src) : runs[r].off);
-      const int hi = cx + 1 < nc[0] ? m.off + (cs[c0 + cx + 2] - m.src) : runs[r + 2].off + runs[r + 2].count;
+      const int hi = cl + 1 < nc[0] ? m.off + (cs[c0 + cl + 2] - m.src) : runs[r + 2].off + runs[r + 2].count;
       s_p[ci][q + 1] = (uint16_t)(hi - s_lo[ci][q]);
     }
     __syncthreads();
@@ -399,7 +425,11 @@ __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4)))
     __syncthreads();
     if (wv == 0) scan_cells(s_cb, ncell);
     __syncthreads();
-    fast = s_words <= kCellChunks && s_cb[ncell] <= kTileChunks;
+    if (s_cb[ncell] <= kTileChunks) break;
+    gw = min(2 * gw, row_cells);
+    __syncthreads();
+    if (tid == 0) s_words = 0;
+    __syncthreads();
   }
   const int words = max(s_words, 1);
   const double4 ref = nt > 0 ? P[a0] : make_double4(0.0, 0.0, 0.0, 0.0);
@@ -470,11 +500,12 @@ __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4)))
           int aw = 0;
           int na = 0, nb = 0;
           float4 at = make_float4(1e18f, 0.f, 0.f, 0.f);   // past the unit: no candidate is near
+          const double4 from = gw > 1 ? P[x0] : ref;       // a tile of wide groups is long
           if (lane < cnt) {
             const double4 pi = P[x0 + lane];
-            at.x = (float)(pi.x - ref.x);
-            at.y = (float)(pi.y - ref.y);
-            at.z = (D == 3) ? (float)(pi.z - ref.z) : 0.0f;
+            at.x = (float)(pi.x - from.x);
+            at.y = (float)(pi.y - from.y);
+            at.z = (D == 3) ? (float)(pi.z - from.z) : 0.0f;
             at.w = (float)pi.w;
             constexpr int q0 = R / 2;            // the atom's own row
             const TileRun m = runs[3 * (q0 + R0) + 1];
@@ -508,9 +539,9 @@ __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(4)))
             const int hc = hc_n, code = code_n;
             const double4 pj = pj_n;
             if (ch + 1 < ch1) load(ch + 1, hc_n, code_n, pj_n);
-            const float px = (float)((pj.x + s_sh[code][0]) - ref.x);
-            const float py = (float)((pj.y + s_sh[code][1]) - ref.y);
-            const float pz = (D == 3) ? (float)((pj.z + s_sh[code][2]) - ref.z) : 0.0f;
+            const float px = (float)((pj.x + s_sh[code][0]) - from.x);
+            const float py = (float)((pj.y + s_sh[code][1]) - from.y);
+            const float pz = (D == 3) ? (float)((pj.z + s_sh[code][2]) - from.z) : 0.0f;
             const bool tb = pj.w != 0.0;
             // a lane without a candidate passes no test
             const float t0 = hc < 0 ? -1.0f : (tb ? thr[0][1] : thr[0][0]);
