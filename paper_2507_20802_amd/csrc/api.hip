@@ -148,7 +148,6 @@ struct Layout {
   int32_t blocks = 0;
   int32_t cells = 0;      // sum of (cell_cap + 1)
   int32_t tiles = 0;      // sum of tile_cap
-  int32_t max_cells = 0;
   std::vector<Geom> geom;
 };
 
@@ -191,7 +190,6 @@ aqs_status make_layout(const aqs_potential* pot, const Tune& tn, int n_rep, cons
     g.tile_off = lo.tiles;
     g.tile_cap = nc[1] * nc[2] * segments_per_row(n, nc[1] * nc[2], kMaxTPA, kFillMin);
     lo.tiles += g.tile_cap;
-    lo.max_cells = std::max(lo.max_cells, g.cell_cap);
     atom_off += g.npad;
     nb_off += (int64_t)g.npad * tn.max_nb;
     block0 += g.nblocks;
@@ -872,7 +870,7 @@ aqs_status rebuild(aqs_ctx* c, Lane& L, const std::vector<int32_t>& sel, bool in
   a.dlx = c->dlx; a.dly = c->dly; a.dlz = c->dlz;
   a.tdlx = c->tdlx; a.tdly = c->tdly; a.tdlz = c->tdlz;
   a.alt4 = c->alt4; a.talt4 = c->talt4;
-  launch_rebuild(a, c->lo.max_cells, L.s, L.nc3_d);
+  launch_rebuild(a, L.s, L.nc3_d);
   HIPCHK(hipGetLastError());
   ++c->cnt.rebuilds;
   for (int r : sel) c->dirty[r] = 0;

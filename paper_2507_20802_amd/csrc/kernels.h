@@ -50,8 +50,7 @@ struct RebuildArgs {
   double4* alt4; double4* talt4;
 };
 
-void launch_rebuild(const RebuildArgs& a, int32_t max_cells_per_slot, hipStream_t s,
-                    const int32_t* nc3_dev);
+void launch_rebuild(const RebuildArgs& a, hipStream_t s, const int32_t* nc3_dev);
 
 // One FIRE iteration: force + control over the force tiles (a.ftiles), then
 // the update over the 256-atom blocks (a.blocks).

@@ -82,3 +82,19 @@ def test_wide_tiles(box, density, rc, tpa, fill, cells, lds):
     sig, E2 = eng.stress(0)
     assert abs(E2 - Eo) <= 1e-12 * max(1.0, np.abs(Eo))
     assert np.allclose(sig, So, rtol=1e-10, atol=1e-12 * scale)
+
+
+def test_crowded_cell():
+    """Several hundred atoms in one cell of an otherwise empty box, loaded in
+    another order than their ids' after a first evaluation."""
+    from paper_2507_20802_amd import Engine, Fire, LJParams, Tuning
+    rng = S.rng_for(2507, 31, 400)
+    g = np.stack(np.meshgrid(np.arange(20), np.arange(20), indexing="ij"), -1).reshape(-1, 2)
+    x = rng.permutation(14.2 + 0.12 * (g + 0.1 * rng.uniform(-1, 1, g.shape)))
+    types = (rng.uniform(size=400) < 0.2).astype(np.uint8)
+    eng = Engine(2, [400], 30.0, 1e-4, pot=LJParams(), fire=Fire(), tuning=Tuning(max_neighbors=512))
+    for y in (x, x[::-1].copy()):
+        eng.set_replica(0, types, y, 0)
+        E, F = eng.energy_forces(0)
+        Eo, Fo, _, _ = O.energy_forces(y, types, O.strain_box(2, 30.0, 0, 1e-4), O.kob_andersen())
+        assert abs(E - Eo) <= 1e-12 * abs(Eo) and np.abs(F - Fo).max() <= 1e-11 * np.abs(Fo).max()
