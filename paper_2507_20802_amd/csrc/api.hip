@@ -56,16 +56,22 @@ constexpr uint32_t kAllXcds = (1u << kXcds) - 1u;
 
 // pinned staging for the records of many small slots (one slot's atoms always fit)
 constexpr size_t kStageBytes = size_t(4) << 20;
-// Iterations of a launch of k_small that no other slot's tiles, check or host
-// prediction waits for (at least; a longer block_iters counts): more than a
-// minimisation mostly takes.  A launch of plain chains then ends with its last
-// chain.  In one of extrapolated starts, which the host makes between two steps,
-// each slot waits for the slowest minimisation of the launch; one that outlasts
-// the launch makes the others wait a second time.  10 extrapolated steps of 8 x
-// 1000 atoms, some over 512 iterations long: 102.4 ms with 512 iterations a
-// launch, 87.7 with 128, 80.8 with 2048; of 64 x 256 atoms 27.0, 31.8 and 25.9
-// (91.6 and 71.3 on tiles, polled every 32).
+// Iterations of a launch of k_small that no tiles wait for (at least; a longer
+// block_iters counts): more than a minimisation mostly takes.  Each launch builds
+// its lists anew (about 85 us for 1000 atoms) and ends with a read-back, and one of
+// plain chains ends with its last chain.  In one of predicted starts, which the
+// host makes between two steps, each slot waits for the slowest minimisation of
+// the launch; one that outlasts the launch makes the others wait a second time.
+// 10 extrapolated steps of 8 x 1000 atoms, some over 512 iterations long: 102.4 ms
+// with 512 iterations a launch, 87.7 with 128, 80.8 with 2048; of 64 x 256 atoms
+// 27.0, 31.8 and 25.9 (91.6 and 71.3 on tiles, polled every 32).  4 learned steps
+// of 1000 atoms: 50.3 ms with 32, 39.2 with 2048 (47.0 on tiles).
 constexpr int kSmallIters = 2048;
+// ... in a live round, whose checks wait for launches to end: rounds of four
+// chains of 4 steps of 1000 atoms 160.8 ms with 32 iterations a launch, 140.5 with
+// 64, 130.3 with 128, 122.8 with 256 (152.3 on tiles), and in the same order where
+// a stress drop ends chains early.
+constexpr int kSmallLive = 256;
 
 // force tiles hold about fill x a block's atom lanes (tuning.tile_fill)
 constexpr double kFillDefault = 0.9, kFillMin = 0.5, kFillMax = 2.0;
@@ -1201,14 +1207,10 @@ aqs_status lane_launch(aqs_ctx* c, Lane& L, int32_t start_mode, bool allow_timed
   L.small_timed = false;
   SideJoined joined{L};
   if (L.nsmall > 0) {
-    // Alone, a plain chain needs the host only at its end and an extrapolated
-    // one at the end of each minimisation, so a launch holds many blocks (a slot
-    // that waits or ends leaves it early, the launch ends with its last slot);
-    // a live round's checks, and the starts whose lists the host rebuilds, wait
-    // for a launch to end, and beside tiles the launch ends with their block.
-    const bool alone = L.tiled.empty() && !c->live &&
-                       (start_mode == AQS_START_PLAIN || start_mode == AQS_START_EXTRAPOLATED);
-    aqs_status st = small_launch(c, L, a, start_mode, alone ? std::max(kSmallIters, M) : M);
+    // A slot that waits for the host or ends leaves its launch early, and the
+    // launch ends with its last slot; beside tiles it ends with their block.
+    const int n = L.tiled.empty() ? std::max(c->live ? kSmallLive : kSmallIters, M) : M;
+    aqs_status st = small_launch(c, L, a, start_mode, n);
     if (st) return st;
   }
   if (timed && !L.tiled.empty()) {

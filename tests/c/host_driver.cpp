@@ -437,17 +437,22 @@ void side_stream_joins(bool destroy) {
   expect(R().small_pending == 0 && R().lost_ops == 0, "destroyed with work in flight");
 }
 
-// A launch of small slots alone outlasts a minimisation, so that a slow one does
-// not make a batch of extrapolated slots wait for it twice; starts whose lists
-// the host rebuilds end it with the block.
-void small_launch_length(int start, bool many) {
+// A launch of small slots alone outlasts a minimisation, so that its lists are
+// not built every few iterations and a slow slot does not make a batch of
+// predicted starts wait for it twice; a live round's launches are shorter, and
+// beside tiles a launch ends with their block.
+void small_launch_length(int start, int32_t live, int least, int most) {
   aqs_tuning tn{};
   tn.block_iters = 8;
-  Case k({100, 100, 100}, tn);
+  Case k({100, 100, 100, 100}, tn);
   k.load_all();
-  const int32_t rep[3] = {0, 1, 2}, steps[3] = {3, 3, 3};
-  call(aqs_minimize_batch(k.c, 3, rep, start, steps, nullptr, nullptr), "minimize");
-  for (int n : R().small_iters) expect(many ? n >= 2048 : n == 8, "the length of a launch");
+  const int32_t rep[3] = {0, 1, 2}, snap[2] = {-1, 3}, steps[3] = {3, 3, 3};
+  aqs_check checks[2];
+  if (live < 0)
+    call(aqs_minimize_batch(k.c, 3, rep, start, steps, nullptr, nullptr), "minimize");
+  else
+    call(aqs_run_round(k.c, 2, rep, snap, steps, start, 1e-4, live, nullptr, checks), "run_round");
+  for (int n : R().small_iters) expect(n >= least && n <= most, "the length of a launch");
   call(aqs_destroy(k.c), "destroy");
 }
 
@@ -477,9 +482,11 @@ int main(int argc, char** argv) {
   else if (what == "slot_loads_wait") slot_loads_wait();
   else if (what == "side_stream_joins") side_stream_joins(false);
   else if (what == "side_stream_joins_destroy") side_stream_joins(true);
-  else if (what == "length_plain") small_launch_length(AQS_START_PLAIN, true);
-  else if (what == "length_extrapolated") small_launch_length(AQS_START_EXTRAPOLATED, true);
-  else if (what == "length_linear") small_launch_length(AQS_START_LINEAR, false);
+  else if (what == "length_plain") small_launch_length(AQS_START_PLAIN, -1, 2048, 2048);
+  else if (what == "length_extrapolated") small_launch_length(AQS_START_EXTRAPOLATED, -1, 2048, 2048);
+  else if (what == "length_linear") small_launch_length(AQS_START_LINEAR, -1, 2048, 2048);
+  else if (what == "length_round") small_launch_length(AQS_START_PLAIN, 0, 2048, 2048);
+  else if (what == "length_live") small_launch_length(AQS_START_PLAIN, 1, 64, 512);
   else if (what == "staging_without_pinned_memory") staging_without_pinned_memory();
   else wrong("no such scenario");
   std::printf("ok\n");
