@@ -788,7 +788,10 @@ aqs_status check_overflow(aqs_ctx* c, Lane& L) {
   return AQS_OK;
 }
 
+// (A write that fails leaves the mirror open: the next call reads what the
+// device has.)
 aqs_status push_state(aqs_ctx* c) {
+  c->synced = false;
   HIPCHK(hipMemcpyAsync(c->d_state, c->h_state, sizeof(State) * c->n_rep, hipMemcpyHostToDevice,
                         c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -799,8 +802,10 @@ aqs_status push_state(aqs_ctx* c) {
 // One slot's state to the device, and the end of what the stream holds waited
 // for: the slot's atoms are loaded, and what went wrong is this call's error.
 aqs_status push_slot(aqs_ctx* c, int32_t rep) {
+  c->synced = false;
   HIPCHK(hipMemcpyAsync(c->d_state + rep, c->h_state + rep, sizeof(State), hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  c->synced = true;   // the callers have read the other slots' states back
   return AQS_OK;
 }
 
@@ -1753,6 +1758,7 @@ aqs_status aqs_affine_shear(aqs_ctx* c, int32_t n_sel, const int32_t* rep, const
       return fail(AQS_EINVAL, "slot %d: a pure shear is only applied forward (dk %lld)", sel[i],
                   (long long)dk[i]);
   }
+  c->synced = false;   // the indices below are the device's once they are written
   // per slot the 2x2 map of (x, y): simple shear F^dk = [[1, dk dgamma], [0, 1]]
   // with dk dgamma in one multiplication (level I, Eq. 18); the pure shear's
   // F^dk by the same square-and-multiply as its box

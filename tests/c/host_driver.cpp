@@ -52,7 +52,7 @@ struct Runtime {
   size_t shmem = 0;
   hipStream_t stream = nullptr;
   // of the scenarios
-  bool fail_capture = false, fail_pinned = false;
+  bool fail_capture = false, fail_pinned = false, fail_uploads = false;
   int small_pending = 0, small_unread = 0;   // k_small: in flight, launched behind one in flight
   std::vector<int> small_iters;
   int lost_ops = 0;                          // operations of streams destroyed with work in them
@@ -278,6 +278,7 @@ static bool is_pinned(const void* p) {
 }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind kind, hipStream_t stream) {
   Stream* s = of(stream);
+  if (kind == hipMemcpyHostToDevice && R().fail_uploads) return R().last = hipErrorUnknown;
   if (kind == hipMemcpyHostToDevice && !is_pinned(src)) {   // staged before the call returns
     std::vector<char> held((const char*)src, (const char*)src + n);
     s->ops.push_back([=] { std::memcpy(dst, held.data(), n); });
@@ -473,6 +474,27 @@ void staging_without_pinned_memory() {
   call(aqs_destroy(k.c), "destroy");
 }
 
+// A call that fails before the device has its states: later calls see the
+// device's, not what the call was about to write.
+void failed_writes_are_not_believed() {
+  Case k({100, 100});
+  k.load_all();
+  const int32_t rep[1] = {0};
+  const int64_t dk[1] = {5};
+  int64_t got = -1;
+  R().fail_uploads = true;
+  expect(aqs_affine_shear(k.c, 1, rep, dk) == AQS_EHIP, "a shear that cannot be uploaded");
+  expect(aqs_set_replica(k.c, 1, k.types[1].data(), k.pos[1].data(), 7) == AQS_EHIP, "a load likewise");
+  R().fail_uploads = false;
+  (void)hipGetLastError();
+  call(aqs_get_strain_index(k.c, 0, &got), "strain_index");
+  expect(got == 0, "the strain index of a shear that failed");
+  call(aqs_affine_shear(k.c, 1, rep, dk), "affine_shear");
+  call(aqs_get_strain_index(k.c, 0, &got), "strain_index");
+  expect(got == 5, "the strain index of a shear");
+  call(aqs_destroy(k.c), "destroy");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -488,6 +510,7 @@ int main(int argc, char** argv) {
   else if (what == "length_round") small_launch_length(AQS_START_PLAIN, 0, 2048, 2048);
   else if (what == "length_live") small_launch_length(AQS_START_PLAIN, 1, 64, 512);
   else if (what == "staging_without_pinned_memory") staging_without_pinned_memory();
+  else if (what == "failed_writes_are_not_believed") failed_writes_are_not_believed();
   else wrong("no such scenario");
   std::printf("ok\n");
   return 0;

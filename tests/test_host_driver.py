@@ -33,7 +33,8 @@ def driver(tmp_path_factory):
 @pytest.mark.parametrize("scenario", ["linear_start_polls", "linear_start_polls_profiled", "slot_loads_wait",
                                       "side_stream_joins", "side_stream_joins_destroy",
                                       "length_plain", "length_extrapolated", "length_linear",
-                                      "length_round", "length_live", "staging_without_pinned_memory"])
+                                      "length_round", "length_live", "staging_without_pinned_memory",
+                                      "failed_writes_are_not_believed"])
 def test_scenario(driver, scenario):
     res = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0 and res.stdout.strip().endswith("ok"), res.stdout + res.stderr
