@@ -119,8 +119,11 @@ typedef struct {
 typedef struct {
   double skin;              /* Verlet skin added to each pair cutoff; 0 = 0.3 */
   int32_t max_neighbors;    /* list capacity per atom; 0 = 64 (2D) / 192 (3D) */
-  int32_t block_iters;      /* FIRE iterations launched between host polls, rounded up to
-                               an even number; 0 = 32 */
+  int32_t block_iters;      /* FIRE iterations launched between host polls, at most, rounded
+                               up to an even number; 0 = 32.  Fewer where all slots of a
+                               launch have lately waited for the host sooner.  Small 2D
+                               slots alone (aqs_small_counters) run up to the larger of
+                               this and 2048, 256 in live rounds.  Changes no result. */
   int32_t use_graph;        /* 1: replay each block of iterations as a hipGraph */
   int32_t max_chain_steps;  /* largest n_steps accepted by aqs_minimize_batch; 0 = 1024 */
   int32_t threads_per_atom; /* force kernel: 1, 2, 4 or 8 lanes per atom; 0 = 2 */
@@ -200,7 +203,8 @@ aqs_status aqs_get_box(aqs_ctx* ctx, int32_t rep, double* H);
 
 /* Copy slot src into slot dst (same atom count, shear mode and dgamma):
  * positions, types, order, strain index and last energy.  Level I anchors
- * and snapshots.  AQS_EINVAL if the slots differ in any of these. */
+ * and snapshots.  AQS_EINVAL if the slots differ in any of these.
+ * Synchronises. */
 aqs_status aqs_copy_replica(aqs_ctx* ctx, int32_t src, int32_t dst);
 
 /* Affine simple shear of the selected slots, Eqs. (2)-(3) with Eq. (16):
@@ -415,15 +419,17 @@ aqs_status aqs_energy_forces(aqs_ctx* ctx, int32_t rep, double* energy,
                              double* forces);
 
 /* Work counters of a context, accumulated since creation or the last reset.
- * Kernel times are measured with HIP events on the context stream around
- * sampled launches (see aqs_set_profiling); launches counts all. */
+ * Kernel times are measured with HIP events recorded with the dispatches of
+ * sampled launches, each on its stream (see aqs_set_profiling); launches
+ * counts all. */
 typedef struct {
   double force_ms;          /* summed duration of the timed force launches */
   int64_t force_timed;      /* force launches timed */
   double update_ms;         /* summed duration of the timed update launches */
   int64_t update_timed;
   int64_t force_launches;   /* force launches issued */
-  int64_t rebuilds;         /* neighbour-list rebuild passes */
+  int64_t rebuilds;         /* neighbour-list rebuild passes, and the lists that small
+                               slots' launches rebuilt */
   int64_t host_polls;       /* state read-backs of the minimisation loop */
   int64_t atom_evals;       /* atoms whose force was evaluated, summed over launches */
   int64_t timed_atom_evals; /* ... over the force launches timed (force_timed) */
@@ -440,8 +446,8 @@ typedef struct {
   int64_t timed_atom_evals; /* atoms whose force the timed launches evaluated */
 } aqs_small_counters;
 
-/* Time every n-th block of FIRE iterations (0 = no timing), on every
- * driver lane's stream (aqs_run_round with live = 1 has two). */
+/* Time every n-th block of iterations (0 = no timing), on every driver
+ * lane's stream (aqs_run_round with live = 1 has two). */
 aqs_status aqs_set_profiling(aqs_ctx* ctx, int32_t every_nth_block);
 
 aqs_status aqs_get_counters(aqs_ctx* ctx, aqs_counters* out, int32_t reset);

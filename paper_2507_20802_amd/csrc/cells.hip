@@ -230,8 +230,8 @@ __global__ __launch_bounds__(kBlock) void k_rb_back(RebuildArgs a) {
 // 64 pairs.  One candidate per lane keeps every lane busy, where a lane per atom
 // left over half of the block idle, read each candidate from LDS once for
 // every atom and sent each entry to memory twice, one by one.  Rebuild of 16 x
-// 32768 atoms (3D, up to 16 of them at once): 535 us, 2246 before; of one
-// replica 67, 256 before.
+// 32768 atoms (3D, 16 of them at once): 497 us, 2156 before; of one replica 55,
+// 197 before.
 // "Cell" above is a group of neighbouring cells of the row where a tile spans
 // more of them than the tables below hold (short cutoffs, tiles filled to the
 // limit): the group's atoms share the candidates around it.
@@ -239,13 +239,22 @@ __global__ __launch_bounds__(kBlock) void k_rb_back(RebuildArgs a) {
 // lists (j | code); so does a tile past the limits below, tested in FP64
 // straight from the cells (kernel's end), and a wide tile of a slot with fewer
 // than two atoms per cell.  There the halo hardly shortens a force launch, and
-// the search takes less time: 2D, 159048 atoms, cutoff 2.5, list kernel and
-// useful force launch, groups against search: 92 and 11.0 us, 61 and 10.9 at 0.8
-// atoms per cell; 88 and 8.1 us, 50 and 9.5 at 2.4, where lists that live over
-// about 25 iterations pay for the groups.
-constexpr int kListBlock = 512;     // threads of the list kernel
-constexpr int kChunkParts = 2;      // a unit's chunks are split over this many wavefronts
-constexpr int kUnitAtoms = 16;      // atoms of one cell that a wavefront tests together
+// the search takes less time: 2D, 159048 atoms, cutoff 2.5, list kernel and mean
+// force launch, groups against search: 92 and 11.0 us, 61 and 10.9 at 0.8 atoms
+// per cell; 88 and 8.1 us, 50 and 9.5 at 2.4, where lists that live over about 25
+// iterations pay for the groups.
+// Times below: a rebuild's list kernel for 32768 atoms in 3D and for 16 of them,
+// 54.6 and 497 us as it is.
+constexpr int kListBlock = 512;     // threads of the list kernel (256: 68 and 673)
+// A unit's chunks are split over this many wavefronts.  1: 54.4 and 479, but 158
+// instead of 146 for one replica of 132651 atoms; 4: 55 and 510, and in 2D 24
+// instead of 20.5 for 4 x 2116 atoms.
+constexpr int kChunkParts = 2;
+// Atoms of one cell that a wavefront tests together: 8: 64 and 566; 32: 48 and 446.
+constexpr int kUnitAtoms = 16;
+// What the tables in LDS hold: a glass's tiles in 3D span 4 to 15 cells of about
+// 11 chunks, in 2D 12 to 25 cells of 2 chunks; two blocks per CU, which the
+// registers allow, fit with them.
 constexpr int kListCells = 96;      // groups of cells in a tile
 constexpr int kTileChunks = 128;    // chunks of all their candidates
 // Cells of a group at first (the chunks may ask for four times as many): FP32
@@ -253,7 +262,9 @@ constexpr int kTileChunks = 128;    // chunks of all their candidates
 // A tile of more cells than 96 such groups goes to the FP64 search.
 constexpr int kGroupCells = 128;
 static_assert(kTileChunks >= kCandCap / kWave, "one group of all candidates fits");
-constexpr int kMaskWords = 2048;    // masks kept at once; larger tiles go in batches of atoms
+// Masks kept at once; larger tiles go in batches of atoms, tested twice (1024: 94 and
+// 634; 4096: as it is).
+constexpr int kMaskWords = 2048;
 
 // Inclusive sum over the lanes of a wavefront.
 __device__ __forceinline__ int wave_scan(int v) {
