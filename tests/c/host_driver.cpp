@@ -44,7 +44,6 @@ struct Runtime {
   std::map<const void*, std::string> names;
   std::map<std::string, int> launched;   // by kernel name, template arguments left out
   std::set<Stream*> streams;
-  std::set<void*> pinned;
   std::map<char*, size_t> pinned_size;
   Stream null_stream;
   hipError_t last = hipSuccess;
